@@ -1011,159 +1011,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 }
 
 // ============================================================================================
-// fp32 path (VALU).
-
-template <int D>
-__global__ __launch_bounds__(256) void bwd_kv_f32_kernel(BwdArgs a) {
-  constexpr int H = D / 2;
-  constexpr int QP = D + 1;
-  __shared__ float Qf[Q_SUB * QP];
-  __shared__ float dOf[Q_SUB * QP];
-  __shared__ float s_lse[Q_SUB], s_del[Q_SUB];
-  __shared__ int s_qpos[Q_SUB];
-  const BkvItem it = a.plan.bkv[blockIdx.x];
-  const int tid = threadIdx.x;
-  const int key = tid >> 1, half = tid & 1;
-  const int hk = it.hk, G = a.s.g;
-  const size_t kv_stride = (size_t)a.s.hkv * D;
-  const int slot = a.plan.kv_list[it.kv_off + min(key, it.nk - 1)];
-  const int kpos = it.kv_pos0 + key;
-  float k[H], v[H], dk[H], dv[H];
-  {
-    const size_t o = (size_t)slot * kv_stride + (size_t)hk * D + half * H;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      k[i] = ((const float*)a.K)[o + i];
-      v[i] = ((const float*)a.V)[o + i];
-      dk[i] = 0.f;
-      dv[i] = 0.f;
-    }
-  }
-  const int* ql = a.plan.q_list + it.q_off;
-  const int nsub = (it.nq + Q_SUB - 1) / Q_SUB;
-  for (int sub = 0; sub < nsub; ++sub)
-    for (int g = 0; g < G; ++g) {
-      const int head = hk * G + g;
-      __syncthreads();
-      for (int e = tid; e < Q_SUB * D; e += blockDim.x) {
-        const int r = e / D, col = e % D;
-        const int row = ql[min(Q_SUB * sub + r, it.nq - 1)];
-        const size_t o = ((size_t)row * a.s.hq + head) * D + col;
-        Qf[r * QP + col] = ((const float*)a.Q)[o];
-        dOf[r * QP + col] = ((const float*)a.dO)[o];
-      }
-      if (tid < Q_SUB) {
-        const int r = Q_SUB * sub + tid;
-        const int row = ql[min(r, it.nq - 1)];
-        s_lse[tid] = a.LSE[(size_t)head * a.s.ns + row];
-        s_del[tid] = a.delta[(size_t)row * a.s.hq + head];
-        s_qpos[tid] = r < it.nq ? a.plan.row_pos[row] : -1;
-      }
-      __syncthreads();
-      for (int r = 0; r < Q_SUB; ++r) {
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-          s = fmaf(Qf[r * QP + half * H + i], k[i], s);
-          dp = fmaf(dOf[r * QP + half * H + i], v[i], dp);
-        }
-        s += __shfl_xor(s, 1);
-        dp += __shfl_xor(dp, 1);
-        float p = expf(s * a.s.scale - s_lse[r]);
-        if (kpos > s_qpos[r]) p = 0.f;
-        const float ds = p * (dp - s_del[r]);
-#pragma unroll
-        for (int i = 0; i < H; ++i) {
-          dv[i] = fmaf(p, dOf[r * QP + half * H + i], dv[i]);
-          dk[i] = fmaf(ds, Qf[r * QP + half * H + i], dk[i]);
-        }
-      }
-    }
-  if (key >= it.nk) return;
-  float* kd;
-  float* vd;
-  if (it.part < 0) {
-    const size_t o = (size_t)slot * kv_stride + (size_t)hk * D + half * H;
-    kd = a.dK + o;
-    vd = a.dV + o;
-  } else {
-    const size_t o = ((size_t)it.part * BKV_TILE + key) * D + half * H;
-    kd = a.part_dk + o;
-    vd = a.part_dv + o;
-  }
-  const bool acc = it.part < 0 && it.acc;   // a cached node's keys: add to earlier calls' gradients
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    kd[i] = dk[i] * a.s.scale + (acc ? kd[i] : 0.f);
-    vd[i] = dv[i] + (acc ? vd[i] : 0.f);
-  }
-}
-
-template <int D>
-__global__ __launch_bounds__(512) void bwd_dq_f32_kernel(BwdArgs a) {
-  constexpr int H = D / 2;
-  constexpr int KP = D + 1;
-  __shared__ float Kf[KV_TILE * KP];
-  __shared__ float Vf[KV_TILE * KP];
-  const FwdItem it = a.plan.fwd[blockIdx.x];
-  const int tid = threadIdx.x, T = blockDim.x;
-  const int pair = tid >> 1, half = tid & 1;
-  const int head = it.head0 + pair / a.s.bmq;
-  const int hk = it.head0 / a.s.g;
-  const int ridx = pair % a.s.bmq;
-  const bool row_ok = ridx < it.nq;
-  const int row = a.plan.q_list[it.q_off + (row_ok ? ridx : it.nq - 1)];
-  const int qpos = a.plan.row_pos[row];
-  const float lse = a.LSE[(size_t)head * a.s.ns + row];
-  const float del = a.delta[(size_t)row * a.s.hq + head];
-  float q[H], dov[H], dq[H];
-  {
-    const size_t o = ((size_t)row * a.s.hq + head) * D + half * H;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      q[i] = ((const float*)a.Q)[o + i];
-      dov[i] = ((const float*)a.dO)[o + i];
-      dq[i] = 0.f;
-    }
-  }
-  const size_t kv_stride = (size_t)a.s.hkv * D;
-  const int* kvl = a.plan.kv_list + it.kv_off;
-  const int ntiles = (it.nkv + KV_TILE - 1) / KV_TILE;
-  for (int t = 0; t < ntiles; ++t) {
-    __syncthreads();
-    for (int e = tid; e < KV_TILE * D; e += T) {
-      const int r = e / D, col = e % D;
-      const int key = min(t * KV_TILE + r, it.nkv - 1);
-      const size_t o2 = (size_t)kvl[key] * kv_stride + (size_t)hk * D + col;
-      Kf[r * KP + col] = ((const float*)a.K)[o2];
-      Vf[r * KP + col] = ((const float*)a.V)[o2];
-    }
-    __syncthreads();
-    for (int j = 0; j < KV_TILE; ++j) {
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int i = 0; i < H; ++i) {
-        s = fmaf(q[i], Kf[j * KP + half * H + i], s);
-        dp = fmaf(dov[i], Vf[j * KP + half * H + i], dp);
-      }
-      s += __shfl_xor(s, 1);
-      dp += __shfl_xor(dp, 1);
-      const int kidx = t * KV_TILE + j;
-      float p = expf(s * a.s.scale - lse);
-      if (kidx >= it.nkv || it.kv_pos0 + kidx > qpos) p = 0.f;
-      const float ds = p * (dp - del);
-#pragma unroll
-      for (int i = 0; i < H; ++i) dq[i] = fmaf(ds, Kf[j * KP + half * H + i], dq[i]);
-    }
-  }
-  if (!row_ok) return;
-  float* dst = it.part < 0 ? a.dQ + ((size_t)row * a.s.hq + head) * D + half * H
-                           : a.part_dq + (((size_t)it.part + ridx) * a.s.hq + head) * D + half * H;
-#pragma unroll
-  for (int i = 0; i < H; ++i) dst[i] = dq[i] * a.s.scale;
-}
-
-// ============================================================================================
 // Delta = rowsum(dO * O) per (row, head) (O + O_lo when the forward's residual is given),
 // LSE * log2(e) for the exp2-based kernels, and the (hi, lo) start values of the dK/dV kernel's
 // accumulators.  (row, head) pairs are walked in memory order (O, dO and O_lo are [Ns][Hq][d], the
@@ -1316,8 +1163,7 @@ hipError_t launch_bwd_kv(const BwdArgs& a, bool bf16, hipStream_t st) {
     if (a.s.d == 128) hipLaunchKernelGGL((bwd_kv_bf16_1w_kernel<128, PSATTN_KV_REM>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((bwd_kv_bf16_1w_kernel<64, PSATTN_KV_REM>), grid, block, 0, st, a);
   } else {
-    if (a.s.d == 128) hipLaunchKernelGGL((bwd_kv_f32_kernel<128>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_kv_f32_kernel<64>), grid, block, 0, st, a);
+    return launch_bwd_kv_f32(a, st);
   }
   return hipGetLastError();
 }
@@ -1332,9 +1178,7 @@ hipError_t launch_bwd_dq(const BwdArgs& a, bool bf16, hipStream_t st) {
     if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<128, NW, 4, PSATTN_DQ_NH>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<64, NW, 4, PSATTN_DQ_NH>), grid, block, 0, st, a);
   } else {
-    const dim3 block(2 * a.s.bmq * a.s.hc);
-    if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_f32_kernel<128>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dq_f32_kernel<64>), grid, block, 0, st, a);
+    return launch_bwd_dq_f32(a, st);
   }
   return hipGetLastError();
 }

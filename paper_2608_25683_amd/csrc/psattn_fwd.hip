@@ -1,4 +1,4 @@
-// Forward kernels: bf16 MFMA main kernel, fp32 VALU kernel, log-sum-exp merge of split pieces.
+// Forward kernels: bf16 MFMA main kernel, log-sum-exp merge of split pieces.
 //
 // bf16 kernels (gfx950).  One workgroup = one FwdItem: 32*rw query rows x hc query heads (all
 // reading one kv head) x a range of keys along the node's root-to-node path.  A wave computes the
@@ -475,87 +475,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 }
 
 // ============================================================================================
-// fp32 path (VALU).  Two lanes per (row, head) pair, each holding half of head_dim.
-
-template <int D>
-__global__ __launch_bounds__(512) void fwd_f32_kernel(FwdArgs a) {
-  constexpr int H = D / 2;
-  constexpr int KP = D + 1;   // LDS row stride (floats)
-  __shared__ float Kf[KV_TILE * KP];
-  __shared__ float Vf[KV_TILE * KP];
-  const FwdItem it = a.plan.fwd[blockIdx.x];
-  const int tid = threadIdx.x, T = blockDim.x;
-  const int pair = tid >> 1, half = tid & 1;
-  const int head = it.head0 + pair / a.s.bmq;
-  const int hk = it.head0 / a.s.g;
-  const int ridx = pair % a.s.bmq;
-  const bool row_ok = ridx < it.nq;
-  const int row = a.plan.q_list[it.q_off + (row_ok ? ridx : it.nq - 1)];
-  const int qpos = a.plan.row_pos[row];
-  float q[H], o[H];
-  const float* qp = (const float*)a.Q + ((size_t)row * a.s.hq + head) * D + half * H;
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    q[i] = qp[i];
-    o[i] = 0.f;
-  }
-  float m_run = kNegInf, l_run = 0.f;
-  const size_t kv_stride = (size_t)a.s.hkv * D;
-  const int* kvl = a.plan.kv_list + it.kv_off;
-  const int ntiles = (it.nkv + KV_TILE - 1) / KV_TILE;
-  for (int t = 0; t < ntiles; ++t) {
-    __syncthreads();
-    for (int e = tid; e < KV_TILE * D; e += T) {
-      const int r = e / D, col = e % D;
-      const int key = min(t * KV_TILE + r, it.nkv - 1);
-      const size_t o2 = (size_t)kvl[key] * kv_stride + (size_t)hk * D + col;
-      Kf[r * KP + col] = ((const float*)a.K)[o2];
-      Vf[r * KP + col] = ((const float*)a.V)[o2];
-    }
-    __syncthreads();
-    float s[KV_TILE];
-    float mloc = kNegInf;
-    for (int j = 0; j < KV_TILE; ++j) {
-      float acc = 0.f;
-#pragma unroll
-      for (int i = 0; i < H; ++i) acc = fmaf(q[i], Kf[j * KP + half * H + i], acc);
-      acc += __shfl_xor(acc, 1);
-      const int kidx = t * KV_TILE + j;
-      if (kidx >= it.nkv || it.kv_pos0 + kidx > qpos) acc = kNegInf;
-      s[j] = acc * a.s.scale;
-      mloc = fmaxf(mloc, s[j]);
-    }
-    const float m_new = fmaxf(m_run, mloc);
-    const float m_use = m_new == kNegInf ? 0.f : m_new;
-    const float alpha = expf(m_run - m_use);
-    l_run *= alpha;
-#pragma unroll
-    for (int i = 0; i < H; ++i) o[i] *= alpha;
-    for (int j = 0; j < KV_TILE; ++j) {
-      const float p = expf(s[j] - m_use);
-      l_run += p;
-#pragma unroll
-      for (int i = 0; i < H; ++i) o[i] = fmaf(p, Vf[j * KP + half * H + i], o[i]);
-    }
-    m_run = m_new;
-  }
-  const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-  const float lse = l_run > 0.f ? m_run + logf(l_run) : kNegInf;
-  if (!row_ok) return;
-  float* op;
-  if (it.part < 0) {
-    op = (float*)a.O + ((size_t)row * a.s.hq + head) * D + half * H;
-    if (half == 0) a.LSE[(size_t)head * a.s.ns + row] = lse;
-  } else {
-    const size_t prow = (size_t)it.part + ridx;
-    op = a.part_o + (prow * a.s.hq + head) * D + half * H;
-    if (half == 0) a.part_lse[prow * a.s.hq + head] = lse;
-  }
-#pragma unroll
-  for (int i = 0; i < H; ++i) op[i] = o[i] * inv;
-}
-
-// ============================================================================================
 // log-sum-exp merge of split forward pieces, fixed piece order
 template <bool BF16>
 __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
@@ -609,9 +528,7 @@ hipError_t launch_fwd_main(const FwdArgs& a, bool bf16, hipStream_t st) {
     if (a.s.d == 128) hipLaunchKernelGGL((fwd_bf16_w64_kernel<128, 8 / PSATTN_FWD_NH, PSATTN_FWD_NS, PSATTN_FWD_NH>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd_bf16_w64_kernel<64, 8 / PSATTN_FWD_NH, PSATTN_FWD_NS, PSATTN_FWD_NH>), grid, block, 0, st, a);
   } else {
-    const dim3 block(2 * a.s.bmq * a.s.hc);  // two lanes per (row, head)
-    if (a.s.d == 128) hipLaunchKernelGGL((fwd_f32_kernel<128>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd_f32_kernel<64>), grid, block, 0, st, a);
+    return launch_fwd_f32(a, st);
   }
   return hipGetLastError();
 }

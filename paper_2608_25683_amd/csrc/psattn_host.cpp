@@ -311,12 +311,14 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   s.hkv = t->hkv;
   s.d = t->d;
   s.g = t->hq / t->hkv;
-  // Heads per forward/dQ item: the largest common divisor of G and 4, and 32-row subtiles per
+  // Heads per bf16 forward/dQ item: the largest common divisor of G and 4, and 32-row subtiles per
   // head rw = 8 / hc (2, 4 or 8).  Every item is then 8 subtile x head pairs, which the
   // eight-wavefront kernels need, and each staged key tile serves 8 x 32 query-head rows.  (For
   // G = 5 or 7 that means one head per item with 256-row query tiles.)
-  s.hc = s.g % 4 == 0 ? 4 : (s.g % 2 == 0 ? 2 : 1);
-  s.rw = 8 / s.hc;
+  // The fp32 kernels take one subtile of one head per workgroup (its four wavefronts split the keys).
+  const bool bf16 = t->dtype == PSATTN_BF16;
+  s.hc = !bf16 ? 1 : s.g % 4 == 0 ? 4 : (s.g % 2 == 0 ? 2 : 1);
+  s.rw = bf16 ? 8 / s.hc : 1;
   s.nw = s.hc * s.rw;
   s.bmq = Q_SUB * s.rw;
   s.scale = t->scale;

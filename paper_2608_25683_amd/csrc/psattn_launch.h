@@ -1,4 +1,4 @@
-// Kernel launchers (defined in psattn_fwd.hip, psattn_bwd.hip and psattn_layer.hip, called by the C ABI).
+// Kernel launchers (defined in psattn_fwd.hip, psattn_bwd.hip, psattn_f32.hip and psattn_layer.hip, called by the C ABI).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -56,6 +56,10 @@ hipError_t launch_bwd_dq(const BwdArgs& a, bool bf16, hipStream_t st);
 hipError_t launch_bwd_reduce_kv(const BwdArgs& a, hipStream_t st);
 hipError_t launch_bwd_reduce_dq(const BwdArgs& a, bool bf16, hipStream_t st);
 hipError_t launch_bwd_zero_pad(const BwdArgs& a, hipStream_t st);
+// the fp32 kernels (psattn_f32.hip), called by the launchers above
+hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t st);
+hipError_t launch_bwd_dq_f32(const BwdArgs& a, hipStream_t st);
+hipError_t launch_bwd_kv_f32(const BwdArgs& a, hipStream_t st);
 // layer steps around the attention (psattn_layer.hip)
 hipError_t launch_rope(const PlanView& plan, int32_t ns, int32_t heads, int32_t d, float theta, bool inverse, bool bf16,
                        void* X, hipStream_t st);
