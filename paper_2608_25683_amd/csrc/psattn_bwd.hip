@@ -1083,7 +1083,8 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a) {
   }
 }
 
-// dK/dV = sum of partial tiles in ascending chunk order (added to dK/dV for a cached node's keys)
+// dK/dV = sum of partial tiles in ascending chunk order (added to dK/dV for a cached node's keys).
+// One 16-byte piece of dK and of dV per thread; the chunks' pieces are read independently.
 __global__ __launch_bounds__(256) void bwd_reduce_kv_kernel(BwdArgs a) {
   const ReduceEntry e = a.plan.reduce[blockIdx.x];
   const int D = a.s.d;
@@ -1091,6 +1092,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kv_kernel(BwdArgs a) {
   for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < e.nk * (D / 4); idx += gridDim.y * blockDim.x) {
     const int k = idx / (D / 4), d4 = (idx % (D / 4)) * 4;
     f32x4 sk = f32x4{}, sv = f32x4{};
+#pragma unroll 4
     for (int j = 0; j < e.nparts; ++j) {
       const size_t o = (((size_t)e.part0 + j) * BKV_TILE + k) * D + d4;
       sk += *(const f32x4*)(a.part_dk + o);
@@ -1107,7 +1109,8 @@ __global__ __launch_bounds__(256) void bwd_reduce_kv_kernel(BwdArgs a) {
 }
 
 // dQ = sum of partial rows in ascending piece order (bf16: also the pieces' row sums of dS', which
-// complete the exact Delta' of the dK/dV kernel, as the dQ kernel does for unsplit rows)
+// complete the exact Delta' of the dK/dV kernel, as the dQ kernel does for unsplit rows).  One
+// 16-byte piece per thread, as bwd_reduce_kv_kernel.
 template <bool BF16>
 __global__ __launch_bounds__(256) void bwd_reduce_dq_kernel(BwdArgs a) {
   const MergeEntry e = a.plan.merge[blockIdx.x];
@@ -1126,6 +1129,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_dq_kernel(BwdArgs a) {
   for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < e.nq * per_row; idx += gridDim.y * blockDim.x) {
     const int i = idx / per_row, r = (idx % per_row) * 4;
     f32x4 acc = f32x4{};
+#pragma unroll 4
     for (int j = 0; j < e.nparts; ++j)
       acc += *(const f32x4*)(a.part_dq + ((size_t)e.part0 + (size_t)j * bmq + i) * hq * D + r);
     const int row = a.plan.q_list[e.q_off + i];
@@ -1184,13 +1188,14 @@ hipError_t launch_bwd_dq(const BwdArgs& a, bool bf16, hipStream_t st) {
 }
 
 hipError_t launch_bwd_reduce_kv(const BwdArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(bwd_reduce_kv_kernel, dim3(a.n_reduce, kMergeSlices), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(bwd_reduce_kv_kernel, dim3(a.n_reduce, merge_slices(a.n_reduce, (int64_t)BKV_TILE * a.s.d / 4, 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_reduce_dq(const BwdArgs& a, bool bf16, hipStream_t st) {
-  if (bf16) hipLaunchKernelGGL(bwd_reduce_dq_kernel<true>, dim3(a.n_merge, kMergeSlices), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(bwd_reduce_dq_kernel<false>, dim3(a.n_merge, kMergeSlices), dim3(256), 0, st, a);
+  const dim3 grid(a.n_merge, merge_slices(a.n_merge, (int64_t)a.max_merge_rows * a.s.hq * a.s.d / 4, 256));
+  if (bf16) hipLaunchKernelGGL(bwd_reduce_dq_kernel<true>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(bwd_reduce_dq_kernel<false>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "psattn_launch.h"
 
 namespace psattn {
@@ -42,7 +44,15 @@ __device__ __forceinline__ void static_for(F&& f) {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_inff();
 constexpr int IDX_BLK = 256;   // slot / row indices staged in LDS per block
-constexpr int kMergeSlices = 8; // workgroups per merge / reduction record (grid y)
+// Workgroups per merge / reduction record (grid y) for records of up to `elements` elements, per_wg
+// of them per turn of a workgroup.  One turn each (its dependent reads are waited for once) as long as
+// the launch has no more than 8192 workgroups, four rounds of a chip that holds 2048; beyond
+// that it is bound by memory and more turns of fewer workgroups are faster (256 records of 16 rows x
+// 32 heads in 5 pieces: 52 us with 8 workgroups each, 58 us with 64), but never fewer than 8.
+inline unsigned merge_slices(int records, int64_t elements, int per_wg) {
+  const int64_t need = (elements + per_wg - 1) / per_wg;
+  return (unsigned)std::min<int64_t>(need, std::max<int64_t>(8, 8192 / records));
+}
 static_assert((IDX_BLK & (IDX_BLK - 1)) == 0, "staged index blocks are addressed modulo 2*IDX_BLK");
 
 __device__ __forceinline__ f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {

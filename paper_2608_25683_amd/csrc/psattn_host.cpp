@@ -66,6 +66,7 @@ struct psattn_tree {
   std::vector<BkvItem> bkv;
   std::vector<ReduceEntry> reduce;
   int64_t fwd_part_rows = 0, bkv_part_tiles = 0;
+  int32_t max_merge_rows = 0;
   // device image of the plan
   size_t o_row_pos = 0, o_row_slot = 0, o_q = 0, o_qpos = 0, o_kv = 0, o_fwd = 0, o_merge = 0, o_bkv = 0, o_reduce = 0, o_pad = 0;
   size_t plan_bytes = 0;
@@ -479,6 +480,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   if (part_rows > INT32_MAX / 2) return fail(PSATTN_E_UNSUPPORTED, "too many partial rows");
   t->fwd_part_rows = part_rows;
   t->merge = merges;
+  t->max_merge_rows = 0;
+  for (const MergeEntry& m : merges) t->max_merge_rows = std::max(t->max_merge_rows, m.nq);
   {
     std::vector<double> c(ftasks.size());
     for (size_t i = 0; i < ftasks.size(); ++i) c[i] = ftasks[i].cost;
@@ -867,6 +870,7 @@ psattn_status psattn_fwd(const psattn_tree* t, const void* Q, const void* K, con
   a.s = t->shape;
   a.n_items = (int32_t)t->fwd.size();
   a.n_merge = (int32_t)t->merge.size();
+  a.max_merge_rows = t->max_merge_rows;
   a.Q = Q;
   a.K = K;
   a.V = V;
@@ -902,6 +906,7 @@ psattn_status psattn_bwd(const psattn_tree* t, const void* Q, const void* K, con
   a.s = t->shape;
   a.n_fwd = (int32_t)t->fwd.size();
   a.n_merge = (int32_t)t->merge.size();
+  a.max_merge_rows = t->max_merge_rows;
   a.n_bkv = (int32_t)t->bkv.size();
   a.n_reduce = (int32_t)t->reduce.size();
   a.n_pad = (int32_t)t->pad_slots.size();

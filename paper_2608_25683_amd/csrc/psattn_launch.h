@@ -10,6 +10,7 @@ struct FwdArgs {
   PlanView plan;
   Shape s;
   int32_t n_items, n_merge;
+  int32_t max_merge_rows;   // rows of the largest merge record
   const void* Q;
   const void* K;
   const void* V;
@@ -25,6 +26,7 @@ struct BwdArgs {
   PlanView plan;
   Shape s;
   int32_t n_fwd, n_merge, n_bkv, n_reduce, n_pad;
+  int32_t max_merge_rows;   // rows of the largest merge record
   const void* Q;
   const void* K;
   const void* V;
