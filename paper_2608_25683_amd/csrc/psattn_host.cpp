@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <numeric>
 #include <string>
@@ -248,6 +249,41 @@ std::vector<int> longest_first(const std::vector<double>& cost) {
   return ord;
 }
 
+// Time of one pass over work items of the given costs on `cus` compute units, in the order of
+// longest_first (each free unit takes the next item).
+double makespan(std::vector<double>& cost, double cus) {
+  const size_t m = (size_t)std::max(1.0, std::round(cus));
+  const double scale = (double)m / std::max(1e-9, cus);   // (a fraction of a unit short or over)
+  std::sort(cost.begin(), cost.end(), std::greater<double>());
+  if (cost.size() <= m) return cost.empty() ? 0.0 : cost[0] * std::max(1.0, cost.size() / cus);
+  std::vector<double> heap(cost.begin(), cost.begin() + (long)m);   // min-heap of the units' end times
+  std::make_heap(heap.begin(), heap.end(), std::greater<double>());
+  double end = cost[0];
+  for (size_t i = m; i < cost.size(); ++i) {
+    std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+    heap.back() += cost[i];
+    end = std::max(end, heap.back());
+    std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+  }
+  return end * scale;
+}
+
+// Time of one work item, measured on one workgroup with the card otherwise idle (microseconds):
+// start-up and write-back, and per 64-key tile of a forward and a dQ item together, or per step (32
+// consumer rows of one query head) of a dK/dV item.  The fp32 dK/dV step is one of a 32-key part.
+struct ItemCost {
+  double fwd0, fwd_tile, bkv0, bkv_step;
+};
+ItemCost item_cost(bool bf16, int d) {
+  if (bf16) return d == 128 ? ItemCost{18, 2.9, 9, 1.1} : ItemCost{9, 2.1, 8, 0.8};
+  return d == 128 ? ItemCost{17, 5.9, 7, 2.4} : ItemCost{12, 3.5, 6, 1.6};
+}
+constexpr double kMergeLaunch = 6.0;      // one more launch on the stream, microseconds
+constexpr double kMergeBytes = 4e6;       // partial results written and read again, bytes per microsecond
+// A finer split has to be expected to be this much faster than a coarser one: the model leaves out
+// what items share in L2 and the spread of their times.
+constexpr double kSplitGain = 0.95;
+
 #ifdef PSATTN_PLAN_CHECKS
 // Opt-in (-DPSATTN_PLAN_CHECKS): every index the kernels derive from the plan lies inside the
 // array or buffer it addresses -- row and slot lists, item ranges, partial rows and tiles.  The
@@ -357,22 +393,6 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   std::vector<FTask> ftasks;
   std::vector<MergeEntry> merges;
   t->q_list.clear();
-  int64_t total_f = 0;
-  for (int n = 0; n < N; ++n)
-    for (int a0 = 0; !t->ext[n] && a0 < t->seg_len[n]; a0 += s.bmq) {
-      int a1 = std::min<int>(t->seg_len[n], a0 + s.bmq);
-      total_f += (int64_t)(a1 - a0) * (t->off[n] + a1);
-    }
-  int64_t split_keys;
-  if (o.fwd_kv_split > 0) {
-    split_keys = ((int64_t)o.fwd_kv_split + KV_TILE - 1) / KV_TILE * KV_TILE;
-  } else if (o.fwd_kv_split < 0) {
-    split_keys = INT64_MAX;
-  } else {
-    // automatic: split only when a single item would dominate an even share of the work
-    int64_t per_cu = total_f * n_chunks / std::max(1, 2 * num_cus);
-    split_keys = std::max<int64_t>(16 * KV_TILE, per_cu / std::max(1, s.bmq) / KV_TILE * KV_TILE);
-  }
   int64_t part_rows = 0;
   // Sibling packing: children of one parent whose segments fill at most half a query tile share
   // the key range [0, off) of their common prefix.  Their rows are packed (first fit, child
@@ -401,13 +421,116 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     }
     flush();
   }
-  auto split_range = [&](int64_t nkv_total) {
-    return split_keys == INT64_MAX ? 1 : (int)((nkv_total + split_keys - 1) / split_keys);
+  // Keys per piece of a key range.  Forced: as asked for.  Automatic: at most cap tiles, in equal
+  // pieces (a range just over the cap is halved, not cut into a full piece and a stub).
+  int64_t cap_tiles = INT64_MAX;   // automatic: the largest piece
+  auto piece_keys = [&](int64_t nkv_total) -> int64_t {
+    if (o.fwd_kv_split < 0) return nkv_total;
+    if (o.fwd_kv_split > 0) return ((int64_t)o.fwd_kv_split + KV_TILE - 1) / KV_TILE * KV_TILE;
+    const int64_t tiles = (nkv_total + KV_TILE - 1) / KV_TILE;
+    const int64_t n = cap_tiles == INT64_MAX ? 1 : (tiles + cap_tiles - 1) / cap_tiles;
+    return (tiles + n - 1) / n * KV_TILE;
   };
+  auto num_pieces = [&](int64_t nkv_total) {
+    const int64_t k = piece_keys(nkv_total);
+    return (int)((nkv_total + k - 1) / k);
+  };
+  const ItemCost ic = item_cost(bf16, t->d);
+  // bytes of the backward workspace (the larger one) with these partial rows and tiles
+  auto bwd_bytes = [&](int64_t rows, int64_t tiles) {
+    return (double)t->Ns * t->hq * 16 + (double)rows * t->hq * (t->d + 1) * 4 + (double)tiles * BKV_TILE * t->d * 8;
+  };
+  constexpr double kNoallocBytes = (double)((int64_t)PSATTN_NOALLOC_SCRATCH_MIB << 20) - 16 * kAlign;
+  // the dK/dV work and the coarse rule of its chunks: a chunk holds at most one CU's share of it, so
+  // that a tile whose consumers fit in one share runs as one item, with no partial tiles to write
+  // and sum
+  std::vector<int64_t> desc_rows(N, 0);   // rows of the (internal) descendants of each node
+  for (int n = N - 1; n >= 0; --n)
+    if (t->parent[n] >= 0) desc_rows[t->parent[n]] += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
+  struct KeyTile { int nk; int64_t nq; };
+  std::vector<KeyTile> key_tiles;
+  int64_t total_b = 0;
+  for (int m = 0; m < N; ++m)
+    for (int b0 = 0; b0 < t->seg_len[m]; b0 += BKV_TILE) {
+      const int nk = std::min(BKV_TILE, t->seg_len[m] - b0);
+      const int64_t nq = desc_rows[m] + (t->ext[m] ? 0 : t->seg_len[m] - b0);
+      key_tiles.push_back({nk, nq});
+      total_b += (int64_t)nk * nq;
+    }
+  int64_t chunk_rows = std::max<int64_t>(2048, total_b * t->hkv / std::max(1, num_cus) / BKV_TILE / Q_SUB * Q_SUB);
+  if (o.bwd_q_chunk > 0) chunk_rows = ((int64_t)o.bwd_q_chunk + Q_SUB - 1) / Q_SUB * Q_SUB;
+  else if (o.bwd_q_chunk < 0) chunk_rows = INT64_MAX;
+  // rows per chunk of a row list: as asked for, or equal chunks of at most chunk_rows
+  auto list_chunk = [&](int64_t nq, int64_t cap) -> int64_t {
+    if (nq <= cap) return nq;
+    if (o.bwd_q_chunk > 0) return cap;
+    const int64_t n = (nq + cap - 1) / cap;
+    return ((nq + n - 1) / n + Q_SUB - 1) / Q_SUB * Q_SUB;
+  };
+  auto part_tiles_of = [&](int64_t cap) {
+    int64_t n = 0;
+    for (const KeyTile& k : key_tiles) {
+      const int64_t c = list_chunk(k.nq, cap), parts = (k.nq + c - 1) / c;
+      if (parts > 1) n += parts * t->hkv;
+    }
+    return n;
+  };
+  if (o.fwd_kv_split == 0) {
+    // Automatic split of the key ranges: whole ranges, or pieces of at most 32, 24, .. 4 tiles,
+    // whichever the items' cost model expects to be over first on the compute units that one head
+    // chunk gets.  A piece costs its start-up and its partial rows, written and read again by the
+    // merge passes; a long range on an idle chip costs more (a 4096-token cached prefix and 48 new
+    // rows: 218 us whole).
+    std::vector<std::pair<int64_t, int>> ranges;   // (keys, rows) of every splittable range
+    std::vector<double> fixed;
+    int64_t rows0 = 0;                             // partial rows there are in any case
+    for (const std::vector<int>& pk : packs) {
+      int rows = 0;
+      for (int n : pk) {
+        rows += t->seg_len[n];
+        fixed.push_back(ic.fwd0 + ic.fwd_tile * (double)((t->seg_len[n] + KV_TILE - 1) / KV_TILE));
+      }
+      ranges.push_back({t->off[pk[0]], rows});
+      rows0 += 2 * s.bmq;
+    }
+    for (int n = 0; n < N; ++n)
+      for (int a0 = 0; !packed[n] && !t->ext[n] && a0 < t->seg_len[n]; a0 += s.bmq) {
+        const int a1 = std::min<int>(t->seg_len[n], a0 + s.bmq);
+        ranges.push_back({t->off[n] + a1, a1 - a0});
+      }
+    const int64_t base_tiles = part_tiles_of(chunk_rows);
+    double best = 0.0;
+    int64_t best_cap = INT64_MAX;
+    for (int64_t cap : {INT64_MAX, (int64_t)32, (int64_t)24, (int64_t)16, (int64_t)12, (int64_t)8, (int64_t)6, (int64_t)4}) {
+      cap_tiles = cap;
+      std::vector<double> c = fixed;
+      double moved = 0.0;
+      int64_t prows = rows0;
+      for (const auto& r : ranges) {
+        const int n = num_pieces(r.first);
+        const int64_t k = piece_keys(r.first);
+        for (int j = 0; j < n; ++j)
+          c.push_back(ic.fwd0 + ic.fwd_tile * (double)((std::min(k, r.first - j * k) + KV_TILE - 1) / KV_TILE));
+        if (n > 1) {
+          moved += 4.0 * n * r.second * t->hq * t->d * 4.0;   // O and dQ pieces, written and read
+          prows += (int64_t)n * s.bmq;
+        }
+      }
+      if (c.size() > 65536) break;
+      if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(rows0, base_tiles) <= kNoallocBytes) break;
+      const double time = makespan(c, (double)num_cus / n_chunks) + (moved > 0 && packs.empty() ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
+      if (cap == INT64_MAX || time < kSplitGain * best) {
+        best = time;
+        best_cap = cap;
+      }
+    }
+    cap_tiles = best_cap;
+  }
   for (const std::vector<int>& pk : packs) {
     const int n0 = pk[0];
     const int64_t pre = t->off[n0];   // the common prefix: every sibling starts at the same position
-    const int npref = split_range(pre);
+    const int npref = num_pieces(pre);
+    const int64_t split_keys = piece_keys(pre);
     const int32_t P = (int32_t)part_rows;
     part_rows += (int64_t)(npref + 1) * s.bmq;
     const int32_t q_pack = (int32_t)t->q_list.size();
@@ -454,7 +577,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       for (int a = a0; a < a1; ++a) t->q_list.push_back((int32_t)(t->row_off[n] + a));
       int64_t nkv_total = t->off[n] + a1;
       int64_t min_qpos = t->off[n] + a0;
-      const int npieces = split_keys == INT64_MAX ? 1 : (int)((nkv_total + split_keys - 1) / split_keys);
+      const int npieces = num_pieces(nkv_total);
+      const int64_t split_keys = piece_keys(nkv_total);
       int32_t part0 = -1;
       if (npieces > 1) {
         part0 = (int32_t)part_rows;
@@ -502,6 +626,16 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     }
   }
 
+  // Launch order, the order of the device's copy: by the key tiles an item takes, not by its rows x keys
+  // (a node's last query tile takes as long as a full one; by rows x keys it started among the
+  // short items and ran on alone: 568 items of up to 36 tiles took 198 us, 124 us of them busy).
+  // The head chunks of a task have one key and stay in order.
+  std::vector<FwdItem> fwd_launch = t->fwd;
+  std::stable_sort(fwd_launch.begin(), fwd_launch.end(), [](const FwdItem& x, const FwdItem& y) {
+    return (x.nkv + KV_TILE - 1) / KV_TILE > (y.nkv + KV_TILE - 1) / KV_TILE;
+  });
+  std::vector<BkvItem> bkv_launch;
+
   // ---------------- dK/dV tasks: key tile x consumer-row chunk ----------------
   // consumer list of node m: every row of every (internal) descendant (node order), then m's own
   // rows from its last position down to 0; the tile starting at key b0 uses the list up to own
@@ -525,27 +659,49 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     cons_len[m] = (int64_t)t->q_list.size() - cons_off[m];
     if (t->q_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "row lists exceed 2^31 entries");
   }
-  int64_t total_b = 0;
-  for (int m = 0; m < N; ++m)
-    for (int b0 = 0; b0 < t->seg_len[m]; b0 += BKV_TILE) {
-      int nk = std::min(BKV_TILE, t->seg_len[m] - b0);
-      total_b += (int64_t)nk * (cons_len[m] - (t->ext[m] ? 0 : b0));
+  if (o.bwd_q_chunk == 0) {
+    // Automatic chunks: the coarse rule's, or at most 1024, 512, .. 32 rows, whichever the cost model
+    // expects to be over first on the compute units that one kv head gets.  A chunk costs its start-up
+    // and a partial tile, written and read again; a list that one unit works through alone costs more
+    // (a 512-token prompt and 8 branches of 96 rows: 96 items on 256 units, the longest 160 steps,
+    // 221 us).
+    const int64_t coarse = chunk_rows;
+    double best = 0.0;
+    for (int64_t cap : {coarse, (int64_t)1024, (int64_t)512, (int64_t)384, (int64_t)256, (int64_t)192, (int64_t)128, (int64_t)96,
+                        (int64_t)64, (int64_t)32}) {
+      if (cap > coarse) continue;
+      std::vector<double> c;
+      double moved = 0.0;
+      int64_t ptiles = 0;
+      for (const KeyTile& k : key_tiles) {
+        const int64_t rows = list_chunk(k.nq, cap);
+        const int parts = (int)((k.nq + rows - 1) / rows);
+        for (int j = 0; j < parts; ++j) {
+          const double steps = (double)((std::min(rows, k.nq - j * rows) + Q_SUB - 1) / Q_SUB) * s.g;
+          const int wgs = bf16 ? 1 : (k.nk + 31) / 32;   // fp32: a workgroup per 32 keys
+          for (int w = 0; w < wgs; ++w) c.push_back(ic.bkv0 + ic.bkv_step * steps);
+        }
+        if (parts > 1) {
+          moved += 2.0 * parts * t->hkv * k.nk * t->d * 8.0;   // dK and dV, written and read
+          ptiles += (int64_t)parts * t->hkv;
+        }
+      }
+      if (c.size() > 65536) break;
+      if (cap != coarse && bwd_bytes(part_rows, ptiles) > kNoallocBytes &&
+          bwd_bytes(part_rows, part_tiles_of(coarse)) <= kNoallocBytes)
+        break;
+      const double time = makespan(c, (double)num_cus / t->hkv) + (ptiles ? kMergeLaunch : 0.0) + moved / kMergeBytes;
+      if (cap == coarse || time < kSplitGain * best) {
+        best = time;
+        chunk_rows = cap;
+      }
     }
-  int64_t chunk_rows;
-  if (o.bwd_q_chunk > 0) {
-    chunk_rows = ((int64_t)o.bwd_q_chunk + Q_SUB - 1) / Q_SUB * Q_SUB;
-  } else if (o.bwd_q_chunk < 0) {
-    chunk_rows = INT64_MAX;
-  } else {
-    // a chunk holds at most one CU's share of the dK/dV work: a tile whose consumers fit in one
-    // share runs as one item, with no partial tiles to write and sum
-    int64_t per_cu = total_b * t->hkv / std::max(1, num_cus);
-    chunk_rows = std::max<int64_t>(2048, per_cu / BKV_TILE / Q_SUB * Q_SUB);
   }
   struct BTask {
     int32_t kv_off, nk, kv_pos0, q_off, nq, mask_lo, mask_hi, part_base, nparts, chunk, acc;
     double cost, key;
     int64_t group;   // tasks of one group (same key and group) are emitted as one run
+    int32_t steps;   // key of the launch order: rows, the largest of a group
   };
   std::vector<BTask> btasks;
   std::vector<ReduceEntry> reduces;
@@ -560,7 +716,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       int64_t nq_total = cons_len[m] - (acc ? 0 : b0);
       // own rows at positions b0 .. b0+nk-2 see only part of the tile: the last nk-1 list entries
       const int64_t mlo = acc ? nq_total : nq_total - (nk - 1), mhi = nq_total;
-      int nparts = chunk_rows == INT64_MAX ? 1 : (int)((nq_total + chunk_rows - 1) / chunk_rows);
+      const int64_t crows = list_chunk(nq_total, chunk_rows);
+      int nparts = (int)((nq_total + crows - 1) / crows);
       int32_t kv_off = (int32_t)(kvoff[m] + t->off[m] + b0);
       int32_t kv_pos0 = (int32_t)(t->off[m] + b0);
       int32_t part_base = -1;
@@ -570,8 +727,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
         for (int hk = 0; hk < t->hkv; ++hk) reduces.push_back({kv_off, nk, hk, part_base + hk * nparts, nparts, acc, {0, 0}});
       }
       for (int j = 0; j < nparts; ++j) {
-        int64_t c0 = nparts > 1 ? j * chunk_rows : 0;
-        int64_t c1 = nparts > 1 ? std::min(nq_total, (j + 1) * chunk_rows) : nq_total;
+        int64_t c0 = nparts > 1 ? j * crows : 0;
+        int64_t c1 = nparts > 1 ? std::min(nq_total, (j + 1) * crows) : nq_total;
         BTask b;
         b.kv_off = kv_off;
         b.nk = nk;
@@ -595,17 +752,20 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     // before it, so their own costs differ).  Every other task keeps its own cost: a leaf's tiles
     // share no rows beyond its own, and the chunks of a split tile are equal already.
     double node_key = 0.0;
+    int32_t node_steps = 0;
     int64_t node_group = -1;
     auto grouped = [&](const BTask& b) { return b.nparts == 1 && desc_len[m] > 0; };
     for (size_t i = first_task; i < btasks.size(); ++i)
       if (grouped(btasks[i])) {
         node_key = std::max(node_key, btasks[i].cost);
+        node_steps = std::max(node_steps, btasks[i].nq);
         if (node_group < 0) node_group = (int64_t)i;
       }
     for (size_t i = first_task; i < btasks.size(); ++i) {
       const bool g = grouped(btasks[i]);
       btasks[i].key = g ? node_key : btasks[i].cost;
       btasks[i].group = g ? node_group : (int64_t)i;
+      btasks[i].steps = g ? node_steps : btasks[i].nq;
     }
   }
   if (part_tiles > INT32_MAX / 2) return fail(PSATTN_E_UNSUPPORTED, "too many partial tiles");
@@ -620,14 +780,23 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       if (btasks[x].key != btasks[y].key) return btasks[x].key > btasks[y].key;
       return btasks[x].group < btasks[y].group;
     });
-    t->bkv.clear();
-    for (int i : ord) {
-      const BTask& b = btasks[i];
-      for (int hk = 0; hk < t->hkv; ++hk) {
-        int32_t part = b.nparts > 1 ? b.part_base + hk * b.nparts + b.chunk : -1;
-        t->bkv.push_back({b.kv_off, b.nk, b.kv_pos0, b.q_off, b.nq, hk, part, b.mask_lo, b.mask_hi, b.acc});
+    auto emit = [&](std::vector<BkvItem>& out) {
+      out.clear();
+      for (int i : ord) {
+        const BTask& b = btasks[i];
+        for (int hk = 0; hk < t->hkv; ++hk) {
+          int32_t part = b.nparts > 1 ? b.part_base + hk * b.nparts + b.chunk : -1;
+          out.push_back({b.kv_off, b.nk, b.kv_pos0, b.q_off, b.nq, hk, part, b.mask_lo, b.mask_hi, b.acc});
+        }
       }
-    }
+    };
+    emit(t->bkv);
+    // launch order, likewise by the steps an item takes: its rows, whatever part of its key tile is full
+    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) {
+      if (btasks[x].steps != btasks[y].steps) return btasks[x].steps > btasks[y].steps;
+      return btasks[x].group < btasks[y].group;
+    });
+    emit(bkv_launch);
   }
 
   // ---------------- slots of this call's blocks that hold no token ----------------
@@ -677,9 +846,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   put(t->o_qpos, &past_list, 4);
   put(t->o_qpos + 4, t->q_pos.data(), t->q_pos.size() * 4);
   put(t->o_kv, t->kv_list.data(), t->kv_list.size() * 4);
-  put(t->o_fwd, t->fwd.data(), t->fwd.size() * sizeof(FwdItem));
+  put(t->o_fwd, fwd_launch.data(), t->fwd.size() * sizeof(FwdItem));
   put(t->o_merge, t->merge.data(), t->merge.size() * sizeof(MergeEntry));
-  put(t->o_bkv, t->bkv.data(), t->bkv.size() * sizeof(BkvItem));
+  put(t->o_bkv, bkv_launch.data(), t->bkv.size() * sizeof(BkvItem));
   put(t->o_reduce, t->reduce.data(), t->reduce.size() * sizeof(ReduceEntry));
   put(t->o_pad, t->pad_slots.data(), t->pad_slots.size() * 4);
   return PSATTN_OK;
