@@ -317,6 +317,14 @@ psattn_status psattn_kv_scatter(const psattn_tree* tree, const void* K_rows, con
 psattn_status psattn_kv_gather(const psattn_tree* tree, const float* dK, const float* dV, float* dK_rows,
                                float* dV_rows, void* stream);
 
+/* An fp32 tensor of n elements as three bf16 planes [3][n] whose sum it is (exactly, above 2^-110):
+ * the operand of a product with a bf16 tensor on the bf16 matrix cores that keeps fp32 precision. */
+psattn_status psattn_split_planes(const float* X, void* planes, int64_t n, void* stream);
+/* Backward of silu(A) * B (bf16 [n]): dM is given as three fp32 terms [3][n] to be added, dA and dB come
+ * as bf16 planes [3][n]. */
+psattn_status psattn_silu_bwd(const float* dM_planes, const void* A, const void* B, void* dA_planes, void* dB_planes,
+                              int64_t n, void* stream);
+
 /* Reference count of every node: the number of samples whose path holds it
  * (Sec. 5.2).  node_refcount has num_nodes entries. */
 psattn_status psattn_tree_refcounts(const psattn_tree* tree, int32_t* node_refcount);

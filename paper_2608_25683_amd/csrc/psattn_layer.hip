@@ -9,6 +9,7 @@
 // fp64 (positions reach 10^4 and beyond), the rotation itself is fp32.
 #include <algorithm>
 
+#include "psattn.h"
 #include "psattn_device.h"
 
 namespace psattn {
@@ -111,6 +112,88 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PlanView plan, int32_t ns,
   }
 }
 
+// ---- fp32 tensors as three bf16 planes, for products with a bf16 tensor on the bf16 matrix cores.
+// x = x1 + x2 + x3 exactly: each plane takes the next 8 bits of x's 24-bit significand (truncation, so
+// that nothing overflows; infinities and NaN stay in x1).  The product of a plane and a bf16 number is
+// exact in fp32, so three bf16 products with fp32 sums hold what one fp32 product holds.
+__device__ __forceinline__ void split3(float x, uint32_t& x1, uint32_t& x2, uint32_t& x3) {
+  const uint32_t u = __float_as_uint(x);
+  const bool special = (u & 0x7f800000u) == 0x7f800000u;
+  const uint32_t h = (u & 0xffff0000u) | (special && (u & 0x007fffffu) ? 0x00400000u : 0u);
+  const float r = special ? 0.f : x - __uint_as_float(u & 0xffff0000u);
+  const uint32_t m = __float_as_uint(r) & 0xffff0000u;
+  const float l = r - __uint_as_float(m);
+  x1 = h >> 16;
+  x2 = m >> 16;
+  x3 = __float_as_uint(l) >> 16;
+}
+
+// four consecutive elements into the three planes (n elements each) at element i
+__device__ __forceinline__ void put_planes(const f32x4& x, bf16_t* y, int64_t n, int64_t i) {
+  uint32_t p[3][4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) split3(x[k], p[0][k], p[1][k], p[2][k]);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) *(u32x2*)(y + j * n + i) = u32x2{p[j][0] | p[j][1] << 16, p[j][2] | p[j][3] << 16};
+}
+
+// (VEC: n is a multiple of 4, four elements per lane and turn; else one)
+__device__ __forceinline__ void put_plane1(float x, bf16_t* y, int64_t n, int64_t i) {
+  uint32_t p[3];
+  split3(x, p[0], p[1], p[2]);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) y[j * n + i] = (bf16_t)p[j];
+}
+
+// y [3][n] = the planes of x [n].  Bound by its 10 bytes per element.
+template <bool VEC>
+__global__ __launch_bounds__(256) void split3_kernel(const float* x, bf16_t* y, int64_t n) {
+  if (!VEC) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) put_plane1(x[i], y, n, i);
+    return;
+  }
+  for (int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < n; i += 4 * (int64_t)gridDim.x * 256)
+    put_planes(*(const f32x4*)(x + i), y, n, i);
+}
+
+// Backward of silu(a) * b: dm = the sum of its planes [3][n], da = dm b (s + a s (1 - s)) and db = dm a s
+// with s = sigmoid(a), written as planes.  Bound by its 28 bytes per element, in place of ten
+// elementwise passes over fp32 tensors.
+template <bool VEC>
+__global__ __launch_bounds__(256) void silu_bwd_kernel(const float* dm, const bf16_t* a, const bf16_t* b, bf16_t* da,
+                                                       bf16_t* db, int64_t n) {
+  auto grads = [](float d, float av, float bv, float& ga, float& gb) {
+    const float s = 1.f / (1.f + expf(-av));
+    ga = d * bv * (s + av * s * (1.f - s));
+    gb = d * av * s;
+  };
+  if (!VEC) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+      float ga, gb;
+      grads(dm[i] + (dm[n + i] + dm[2 * n + i]), bf2f(a[i]), bf2f(b[i]), ga, gb);
+      put_plane1(ga, da, n, i);
+      put_plane1(gb, db, n, i);
+    }
+    return;
+  }
+  for (int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < n; i += 4 * (int64_t)gridDim.x * 256) {
+    const f32x4 d = *(const f32x4*)(dm + i) + (*(const f32x4*)(dm + n + i) + *(const f32x4*)(dm + 2 * n + i));
+    const u32x2 a2 = ld8(a + i), b2 = ld8(b + i);
+    f32x4 ga, gb;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float av = k & 1 ? __uint_as_float(a2[k / 2] & 0xffff0000u) : bf2f(a2[k / 2] & 0xffffu);
+      const float bv = k & 1 ? __uint_as_float(b2[k / 2] & 0xffff0000u) : bf2f(b2[k / 2] & 0xffffu);
+      float x, y;
+      grads(d[k], av, bv, x, y);
+      ga[k] = x;
+      gb[k] = y;
+    }
+    put_planes(ga, da, n, i);
+    put_planes(gb, db, n, i);
+  }
+}
+
 unsigned grid_for(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 8192); }
 
 }  // namespace
@@ -133,3 +216,43 @@ hipError_t launch_kv_move(const PlanView& plan, int32_t ns, int32_t row_bytes, b
 }
 
 }  // namespace psattn
+
+// ---------------------------------------------------------------------------------------------
+// C ABI of the steps that need no tree
+
+namespace psattn {
+psattn_status set_error(psattn_status st, const char* msg);
+
+namespace {
+bool misaligned16(const void* p) { return ((uintptr_t)p & 15) != 0; }
+psattn_status launched(const char* what) {
+  const hipError_t e = hipGetLastError();
+  if (e == hipSuccess) return PSATTN_OK;
+  return set_error(PSATTN_E_HIP, what);
+}
+unsigned plane_grid(int64_t n) { return (unsigned)std::min<int64_t>((n % 4 ? n + 255 : n / 4 + 255) / 256, 65536); }
+}  // namespace
+}  // namespace psattn
+
+extern "C" psattn_status psattn_split_planes(const float* X, void* planes, int64_t n, void* stream) {
+  using namespace psattn;
+  if (!X || !planes) return set_error(PSATTN_E_INVALID_ARG, "NULL argument");
+  if (n < 1) return set_error(PSATTN_E_INVALID_ARG, "n must be >= 1");
+  if (misaligned16(X) || misaligned16(planes)) return set_error(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
+  hipLaunchKernelGGL(n % 4 ? split3_kernel<false> : split3_kernel<true>, dim3(plane_grid(n)), dim3(256), 0,
+                     (hipStream_t)stream, X, (dev::bf16_t*)planes, n);
+  return launched("split3 launch failed");
+}
+
+extern "C" psattn_status psattn_silu_bwd(const float* dM_planes, const void* A, const void* B, void* dA_planes,
+                                         void* dB_planes, int64_t n, void* stream) {
+  using namespace psattn;
+  if (!dM_planes || !A || !B || !dA_planes || !dB_planes) return set_error(PSATTN_E_INVALID_ARG, "NULL argument");
+  if (n < 1) return set_error(PSATTN_E_INVALID_ARG, "n must be >= 1");
+  if (misaligned16(dM_planes) || misaligned16(A) || misaligned16(B) || misaligned16(dA_planes) || misaligned16(dB_planes))
+    return set_error(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
+  hipLaunchKernelGGL(n % 4 ? silu_bwd_kernel<false> : silu_bwd_kernel<true>, dim3(plane_grid(n)), dim3(256), 0,
+                     (hipStream_t)stream, dM_planes,
+                     (const dev::bf16_t*)A, (const dev::bf16_t*)B, (dev::bf16_t*)dA_planes, (dev::bf16_t*)dB_planes, n);
+  return launched("silu_bwd launch failed");
+}

@@ -79,38 +79,67 @@ class SharedLayer:
         saved = dict(X=X, r1=r1, h=h, q=q, o=o, o_lo=o_lo, lse=lse, y=y, r2=r2, z=z, a=a, b=b, m=m, K=K_pool, V=V_pool)
         return out, saved
 
+    def _products(self, dt):
+        """(weight gradient x^T g, input gradient g w^T, planes of g) for fp32 g and x, w of the layer's
+        dtype.  fp32: library fp32 products.  bf16: g goes in as its three bf16 planes (psattn_split_planes) and
+        the products run on the bf16 matrix cores with fp32 sums, which an fp32 product of the same
+        numbers, x and w widened first, takes three times as long for.  The input gradient comes as the
+        planes' three terms."""
+        import torch
+        f32 = torch.float32
+        if dt != torch.bfloat16:
+            return (lambda x, g: x.t() @ g), (lambda g, w, add=None: g @ w.t() if add is None else add + g @ w.t()), (lambda g: g)
+
+        def wgrad(x3, g3):
+            return torch.mm(x3.detach().t(), g3, out_dtype=f32)
+
+        def igrad(g3, w, add=None):
+            wt = w.detach().t()
+            return torch.mm(g3, wt, out_dtype=f32) if add is None else torch.addmm(add, g3, wt, out_dtype=f32, out=add)
+        return wgrad, igrad, (lambda g: P.psattn_split_planes(g.detach().contiguous()))
+
     def backward(self, tree: P.Tree, saved, dout):
         """dX [Ns, H] and the weight gradients for the summed upstream gradient dout [Ns, H]."""
         import torch
         W, ns, hq, hkv, d = self.W, tree.num_rows, self.hq, self.hkv, self.d
         s = saved
+        dt = s["q"].dtype
+        bf16 = dt == torch.bfloat16
         f = lambda t: t.float()
+        wgrad, igrad, planes = self._products(dt)
+        rows = (lambda x: x.repeat(3, 1)) if bf16 else (lambda x: x)      # x against each plane of a gradient
+        total = (lambda t: t.view(3, ns, -1).sum(0)) if bf16 else (lambda t: t)
         g = {}
         dout = f(dout)
-        g["W2"] = f(s["m"]).t() @ dout
-        dm = dout @ f(W["W2"]).t()
-        a, b = f(s["a"]), f(s["b"])
-        sig = torch.sigmoid(a)
-        da = dm * b * (sig + a * sig * (1 - sig))
-        db = dm * a * sig
-        z = f(s["z"])
-        g["W1"], g["W3"] = z.t() @ da, z.t() @ db
-        dz = da @ f(W["W1"]).t() + db @ f(W["W3"]).t()
+        p = planes(dout)
+        g["W2"] = wgrad(rows(s["m"]), p)
+        dm = igrad(p, W["W2"])
+        a, b = s["a"], s["b"]
+        if bf16:
+            da, db = P.psattn_silu_bwd(dm, a.detach(), b.detach())
+        else:
+            sig = torch.sigmoid(a)
+            da = dm * b * (sig + a * sig * (1 - sig))
+            db = dm * a * sig
+        z = rows(s["z"])
+        g["W1"], g["W3"] = wgrad(z, da), wgrad(z, db)
+        dz = total(igrad(db, W["W3"], igrad(da, W["W1"])))
         yn = f(s["y"]) * s["r2"]
         g["g2"] = (dz * yn).sum(0)
         dzh = dz * f(W["g2"])
         dy = dout + (dzh - yn * (dzh * yn).mean(-1, keepdim=True)) * s["r2"]
         o = s["o"]
-        g["Wo"] = f(o.view(ns, hq * d)).t() @ dy
-        do = (dy @ f(W["Wo"]).t()).view(ns, hq, d).to(o.dtype).contiguous()
+        p = planes(dy)
+        g["Wo"] = wgrad(rows(o.view(ns, hq * d)), p)
+        do = total(igrad(p, W["Wo"])).view(ns, hq, d).to(o.dtype).contiguous()
         dq, dKp, dVp = P.psattn_bwd(tree, s["q"], s["K"], s["V"], o, s["lse"], do, O_lo=s["o_lo"])
         dk, dv = P.psattn_kv_gather(tree, dKp, dVp)
         P.psattn_rope(tree, dq, self.theta, inverse=True)
         P.psattn_rope(tree, dk, self.theta, inverse=True)
-        h = f(s["h"])
-        dq2, dk2, dv2 = dq.view(ns, hq * d), dk.view(ns, hkv * d), dv.view(ns, hkv * d)
-        g["Wq"], g["Wk"], g["Wv"] = h.t() @ dq2, h.t() @ dk2, h.t() @ dv2
-        dh = dq2 @ f(W["Wq"]).t() + dk2 @ f(W["Wk"]).t() + dv2 @ f(W["Wv"]).t()
+        h = rows(s["h"])
+        dq2, dk2, dv2 = planes(dq.view(ns, hq * d)), planes(dk.view(ns, hkv * d)), planes(dv.view(ns, hkv * d))
+        g["Wq"], g["Wk"], g["Wv"] = wgrad(h, dq2), wgrad(h, dk2), wgrad(h, dv2)
+        dh = total(igrad(dv2, W["Wv"], igrad(dk2, W["Wk"], igrad(dq2, W["Wq"]))))
         xn = f(s["X"]) * s["r1"]
         g["g1"] = (dh * xn).sum(0)
         dhh = dh * f(W["g1"])

@@ -40,6 +40,7 @@ EXPORTED = [
     "psattn_kvm_plan", "psattn_kvm_destroy", "psattn_kvm_call_desc", "psattn_kvm_events", "psattn_kvm_get_stats",
     "psattn_sched_fit", "psattn_sched_group_costs", "psattn_sched_place", "psattn_sched_microbatch",
     "psattn_sched_mb_get", "psattn_sched_mb_destroy", "psattn_rope", "psattn_kv_scatter", "psattn_kv_gather",
+    "psattn_split_planes", "psattn_silu_bwd",
 ]
 
 KVM_EVENTS = {0: "alloc", 1: "refill", 2: "evict", 3: "free"}
@@ -164,6 +165,8 @@ def lib() -> ctypes.CDLL:
         L.psattn_rope.argtypes = [vp, vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_float, ctypes.c_int32, vp]
         L.psattn_kv_scatter.argtypes = [vp, vp, vp, vp, vp, vp]
         L.psattn_kv_gather.argtypes = [vp, vp, vp, vp, vp, vp]
+        L.psattn_split_planes.argtypes = [vp, vp, ctypes.c_int64, vp]
+        L.psattn_silu_bwd.argtypes = [vp, vp, vp, vp, vp, ctypes.c_int64, vp]
         L.psattn_sched_mb_destroy.restype = None
         for name in EXPORTED:
             if name not in ("psattn_tree_destroy", "psattn_status_string", "psattn_last_error"):
@@ -544,6 +547,29 @@ def psattn_kv_gather(tree: Tree, dK, dV, dK_rows=None, dV_rows=None):
     _check(lib().psattn_kv_gather(tree.handle, _vp(dK), _vp(dV), _vp(dK_rows), _vp(dV_rows),
                                   ctypes.c_void_p(torch.cuda.current_stream(dK.device).cuda_stream)))
     return dK_rows, dV_rows
+
+
+def psattn_split_planes(X):
+    """fp32 X [n, c] -> its three bf16 planes [3 n, c], whose sum it is."""
+    import torch
+    _need(X, X.shape, torch.float32, "X")
+    out = torch.empty((3 * X.shape[0], X.shape[1]), dtype=torch.bfloat16, device=X.device)
+    _check(lib().psattn_split_planes(_vp(X), _vp(out), X.numel(), ctypes.c_void_p(torch.cuda.current_stream(X.device).cuda_stream)))
+    return out
+
+
+def psattn_silu_bwd(dM, A, B):
+    """Planes of dA and dB ([3 n, c] bf16) of silu(A) * B (bf16 [n, c]) for the three fp32 terms dM [3 n, c]."""
+    import torch
+    n, c = A.shape
+    _need(dM, (3 * n, c), torch.float32, "dM")
+    _need(A, (n, c), torch.bfloat16, "A")
+    _need(B, (n, c), torch.bfloat16, "B")
+    dA = torch.empty((3 * n, c), dtype=torch.bfloat16, device=A.device)
+    dB = torch.empty_like(dA)
+    _check(lib().psattn_silu_bwd(_vp(dM), _vp(A), _vp(B), _vp(dA), _vp(dB), A.numel(),
+                                 ctypes.c_void_p(torch.cuda.current_stream(A.device).cuda_stream)))
+    return dA, dB
 
 
 def psattn_profile_enable(on: bool = True) -> None:
