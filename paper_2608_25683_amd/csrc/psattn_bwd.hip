@@ -662,19 +662,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int rwn = a.s.rw / NH;                   // NH*32-row blocks per head
-  const int head = it.head0 + wave / rwn;
-  const int hk = it.head0 / a.s.g;
-  const int nkv = it.nkv;
+  const ItemUnits un = item_units(a.s, a.plan, it);
+  const int hk = un.hk;
+  const int nkv = un.nkv;
   const int* kvl = a.plan.kv_list + it.kv_off;
   const int ntiles = (nkv + KV_TILE - 1) / KV_TILE;
 
-  for (int i = tid; i < IDX_BLK; i += NW * 64) {
-    s_slot[0][i] = kvl[min(i, nkv - 1)];
-    if (nkv > IDX_BLK) s_slot[1][i] = kvl[min(IDX_BLK + i, nkv - 1)];
+  for (int i = tid; i < IDX_BLK; i += NW * 64) {   // (it.nkv: known before the item's own range)
+    s_slot[0][i] = kvl[min(i, it.nkv - 1)];
+    if (it.nkv > IDX_BLK) s_slot[1][i] = kvl[min(IDX_BLK + i, it.nkv - 1)];
   }
 
-  int ridx[NH], row[NH], lim[NH];
+  int ridx[NH], row[NH], lim[NH], head[NH];
   bool row_ok[NH];
   float lse2[NH], del[NH];
   // sum over this lane's keys of dS' = P (dP - Delta), with Delta = dO . O from the bf16 O: the
@@ -683,13 +682,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   bf16x8 qreg[NH][KS], doreg[NH][KS];
 #pragma unroll
   for (int rh = 0; rh < NH; ++rh) {
-    ridx[rh] = (wave % rwn) * (32 * NH) + 32 * rh + l32;
+    const int st = un.subtile(a.s, wave * NH + rh, head[rh]);
+    ridx[rh] = 32 * st + l32;
     row_ok[rh] = ridx[rh] < it.nq;
     row[rh] = a.plan.q_list[it.q_off + (row_ok[rh] ? ridx[rh] : it.nq - 1)];
     lim[rh] = min(nkv - 1, a.plan.row_pos[row[rh]] - it.kv_pos0);
-    lse2[rh] = a.lse2[(size_t)row[rh] * a.s.hq + head];
-    del[rh] = a.delta[(size_t)row[rh] * a.s.hq + head];
-    const size_t o = ((size_t)row[rh] * a.s.hq + head) * D + 8 * hh;
+    lse2[rh] = a.lse2[(size_t)row[rh] * a.s.hq + head[rh]];
+    del[rh] = a.delta[(size_t)row[rh] * a.s.hq + head[rh]];
+    const size_t o = ((size_t)row[rh] * a.s.hq + head[rh]) * D + 8 * hh;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qreg[rh][s] = as_bf(ld16((const bf16_t*)a.Q + o + 16 * s));
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
           t * KV_TILE + 32, masked, kcopies, Flag<true>{});
   };
   int t = 0;
-  for (; t < min(it.nfull, ntiles); ++t) tile(t, Flag<false>{});
+  for (; t < min(un.nfull, ntiles); ++t) tile(t, Flag<false>{});
   for (; t < ntiles; ++t) tile(t, Flag<true>{});
   // the last stage's S and dP MFMAs (of the block past the end) have no readers: their registers
   // may be reused at once, so let them finish first (scheduling barriers keep the epilogue's
@@ -966,9 +966,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
       if (it.part < 0) {
         const uint32_t w = split_bf16(-del[rh]);
         const float d0 = bf2f(w & 0xffffu) + bf2f(w >> 16);   // the -Delta the dP products started from
-        ((uint32_t*)a.kv_nd)[(size_t)row[rh] * a.s.hq + head] = split_bf16(d0 - e);
+        ((uint32_t*)a.kv_nd)[(size_t)row[rh] * a.s.hq + head[rh]] = split_bf16(d0 - e);
       } else {
-        a.part_eps[((size_t)it.part + ridx[rh]) * a.s.hq + head] = e;
+        a.part_eps[((size_t)it.part + ridx[rh]) * a.s.hq + head[rh]] = e;
       }
     }
   }
@@ -985,8 +985,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 #pragma unroll
     for (int rh = 0; rh < NH; ++rh) {
       if (!row_ok[rh]) continue;
-      float* dst = it.part < 0 ? a.dQ + ((size_t)row[rh] * a.s.hq + head) * D
-                               : a.part_dq + (((size_t)it.part + ridx[rh]) * a.s.hq + head) * D;
+      float* dst = it.part < 0 ? a.dQ + ((size_t)row[rh] * a.s.hq + head[rh]) * D
+                               : a.part_dq + (((size_t)it.part + ridx[rh]) * a.s.hq + head[rh]) * D;
 #pragma unroll
       for (int mb = 0; mb < DB; ++mb)
 #pragma unroll
@@ -1009,8 +1009,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
         *(f32x4*)(qrow + 4 * (32 * mb + 8 * g4 + 4 * hh)) =
             f32x4{dq[rh][mb][4 * g4] * scale, dq[rh][mb][4 * g4 + 1] * scale, dq[rh][mb][4 * g4 + 2] * scale,
                   dq[rh][mb][4 * g4 + 3] * scale};
-    const size_t dsto = it.part < 0 ? ((size_t)row[rh] * a.s.hq + head) * D
-                                    : (((size_t)it.part + ridx[rh]) * a.s.hq + head) * D;
+    const size_t dsto = it.part < 0 ? ((size_t)row[rh] * a.s.hq + head[rh]) * D
+                                    : (((size_t)it.part + ridx[rh]) * a.s.hq + head[rh]) * D;
     float* const base = it.part < 0 ? a.dQ : a.part_dq;
     const int ch = lane % CPRQ;
 #pragma unroll
@@ -1191,7 +1191,7 @@ hipError_t launch_bwd_dq(const BwdArgs& a, bool bf16, hipStream_t st) {
   const dim3 grid(a.n_fwd);
   if (bf16) {
     // 8 / NH waves of NH*32 rows (the planner makes every item 8 (subtile, head) pairs)
-    if (a.s.rw % PSATTN_DQ_NH != 0 || a.s.nw != 8) return hipErrorInvalidValue;
+    if (a.s.nw != 8) return hipErrorInvalidValue;
     constexpr int NW = 8 / PSATTN_DQ_NH;
     const dim3 block(NW * 64);
     if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<128, NW, 4, PSATTN_DQ_NH>), grid, block, 0, st, a);

@@ -1,7 +1,7 @@
 // Forward kernels: bf16 MFMA main kernel, log-sum-exp merge of split pieces.
 //
-// bf16 kernels (gfx950).  One workgroup = one FwdItem: 32*rw query rows x hc query heads (all
-// reading one kv head) x a range of keys along the node's root-to-node path.  A wave computes the
+// bf16 kernels (gfx950).  One workgroup = one FwdItem: 8 (32-row subtile, query head) units of a query
+// tile, all reading one kv head (item_units), x a range of keys along the node's root-to-node path.  A wave computes the
 // transposed score tile S^T = K Q^T with v_mfma_f32_32x32x16_bf16, so each lane holds one query
 // row: softmax statistics are per-lane scalars and one v_permlane32_swap completes each row
 // reduction.  The probabilities leave the accumulators as the B operand of O^T += V^T P^T without
@@ -63,29 +63,29 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int rwn = a.s.rw / NH;                   // NH*32-row blocks per head
-  const int head = it.head0 + wave / rwn;
-  const int hk = it.head0 / a.s.g;
-  const int nkv = it.nkv;
+  const ItemUnits un = item_units(a.s, a.plan, it);
+  const int hk = un.hk;
+  const int nkv = un.nkv;
   const int* kvl = a.plan.kv_list + it.kv_off;
   const int ntiles = (nkv + KV_TILE - 1) / KV_TILE;
 
-  for (int i = tid; i < IDX_BLK; i += NW * 64) {
-    s_slot[0][i] = kvl[min(i, nkv - 1)];
-    if (nkv > IDX_BLK) s_slot[1][i] = kvl[min(IDX_BLK + i, nkv - 1)];
+  for (int i = tid; i < IDX_BLK; i += NW * 64) {   // (it.nkv: known before the item's own range)
+    s_slot[0][i] = kvl[min(i, it.nkv - 1)];
+    if (it.nkv > IDX_BLK) s_slot[1][i] = kvl[min(IDX_BLK + i, it.nkv - 1)];
   }
 
-  int ridx[NH], row[NH], lim[NH];
+  int ridx[NH], row[NH], lim[NH], head[NH];
   bool row_ok[NH];
   bf16x8 qreg[NH][KS];
 #pragma unroll
   for (int rh = 0; rh < NH; ++rh) {
-    ridx[rh] = (wave % rwn) * (32 * NH) + 32 * rh + l32;
+    const int st = un.subtile(a.s, wave * NH + rh, head[rh]);
+    ridx[rh] = 32 * st + l32;
     row_ok[rh] = ridx[rh] < it.nq;
     row[rh] = a.plan.q_list[it.q_off + (row_ok[rh] ? ridx[rh] : it.nq - 1)];
     // key kidx of this item is visible to the row iff kidx <= lim
     lim[rh] = min(nkv - 1, a.plan.row_pos[row[rh]] - it.kv_pos0);
-    const bf16_t* qp = (const bf16_t*)a.Q + ((size_t)row[rh] * a.s.hq + head) * D + 8 * hh;
+    const bf16_t* qp = (const bf16_t*)a.Q + ((size_t)row[rh] * a.s.hq + head[rh]) * D + 8 * hh;
 #pragma unroll
     for (int s = 0; s < KS; ++s) qreg[rh][s] = as_bf(ld16(qp + 16 * s));
   }
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     stage(SB, SA, PA, PB, Kt + 32 * RB, &smem[(t + 1) % NS][0][0], Vt, t * KV_TILE + 32, masked, vcopies, Flag<true>{});
   };
   int t = 0;
-  for (; t < min(it.nfull, ntiles); ++t) tile(t, Flag<false>{});
+  for (; t < min(un.nfull, ntiles); ++t) tile(t, Flag<false>{});
   for (; t < ntiles; ++t) tile(t, Flag<true>{});
   wait_vmem<0>();   // no copy may still be writing this workgroup's LDS when it ends
   // PV of the last block
@@ -416,13 +416,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     inv[rh] = l_tot > 0.f ? 1.f / l_tot : 0.f;
     const float lse = l_tot > 0.f ? m_run[rh] * a.s.scale + logf(l_tot) : kNegInf;
     if (direct) {
-      if (row_ok[rh] && hh == 0) a.LSE[(size_t)head * a.s.ns + row[rh]] = lse;
+      if (row_ok[rh] && hh == 0) a.LSE[(size_t)head[rh] * a.s.ns + row[rh]] = lse;
       continue;
     }
     if (!row_ok[rh]) continue;
     {
       const size_t prow = (size_t)it.part + ridx[rh];
-      float* op = a.part_o + (prow * a.s.hq + head) * D;
+      float* op = a.part_o + (prow * a.s.hq + head[rh]) * D;
 #pragma unroll
       for (int mb = 0; mb < DB; ++mb)
 #pragma unroll
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
           *(f32x4*)(op + 32 * mb + 8 * g4 + 4 * hh) =
               f32x4{oacc[rh][mb][4 * g4] * inv[rh], oacc[rh][mb][4 * g4 + 1] * inv[rh], oacc[rh][mb][4 * g4 + 2] * inv[rh],
                     oacc[rh][mb][4 * g4 + 3] * inv[rh]};
-      if (hh == 0) a.part_lse[prow * a.s.hq + head] = lse;
+      if (hh == 0) a.part_lse[prow * a.s.hq + head[rh]] = lse;
     }
   }
   if (direct) {
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
         const int r = __shfl(row[rh], rl % 32);
         const int ok = __shfl((int)row_ok[rh], rl % 32);
         const u32x4 v = *(const u32x4*)(ot + rl * OS + 16 * ch);
-        if (ok) *(u32x4*)(dst + ((size_t)r * a.s.hq + head) * RB + 16 * ch) = v;
+        if (ok) *(u32x4*)(dst + ((size_t)r * a.s.hq + head[rh]) * RB + 16 * ch) = v;
       }
     };
     __syncthreads();
@@ -543,7 +543,7 @@ hipError_t launch_fwd_main(const FwdArgs& a, bool bf16, hipStream_t st) {
   if (bf16) {
     // 8 / NH waves of NH*32 rows (the planner makes every item 8 (subtile, head) pairs); the pools
     // are addressed by 32-bit byte offsets (the host rejects larger trees)
-    if (a.s.rw % PSATTN_FWD_NH != 0 || a.s.nw != 8) return hipErrorInvalidValue;
+    if (a.s.nw != 8) return hipErrorInvalidValue;
     const dim3 block(8 / PSATTN_FWD_NH * 64);
     if (a.s.d == 128) hipLaunchKernelGGL((fwd_bf16_w64_kernel<128, 8 / PSATTN_FWD_NH, PSATTN_FWD_NS, PSATTN_FWD_NH>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((fwd_bf16_w64_kernel<64, 8 / PSATTN_FWD_NH, PSATTN_FWD_NS, PSATTN_FWD_NH>), grid, block, 0, st, a);

@@ -68,6 +68,7 @@ struct psattn_tree {
   std::vector<ReduceEntry> reduce;
   int64_t fwd_part_rows = 0, bkv_part_tiles = 0;
   int32_t max_merge_rows = 0;
+  int32_t n_fwd_launch = 0;   // forward / dQ items in the device image (those with rows)
   // device image of the plan
   size_t o_row_pos = 0, o_row_slot = 0, o_q = 0, o_qpos = 0, o_kv = 0, o_fwd = 0, o_merge = 0, o_bkv = 0, o_reduce = 0, o_pad = 0;
   size_t plan_bytes = 0;
@@ -630,10 +631,25 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // (a node's last query tile takes as long as a full one; by rows x keys it started among the
   // short items and ran on alone: 568 items of up to 36 tiles took 198 us, 124 us of them busy).
   // The head chunks of a task have one key and stay in order.
-  std::vector<FwdItem> fwd_launch = t->fwd;
-  std::stable_sort(fwd_launch.begin(), fwd_launch.end(), [](const FwdItem& x, const FwdItem& y) {
-    return (x.nkv + KV_TILE - 1) / KV_TILE > (y.nkv + KV_TILE - 1) / KV_TILE;
-  });
+  // bf16 items hold 8 (subtile, head) units of their tile, subtile by subtile (item_units in the
+  // kernels): an item's keys end at its last row, and one whose units all lie past the tile's last row
+  // is not launched.
+  std::vector<std::pair<int64_t, int>> launch;   // (key tiles, item)
+  for (size_t i = 0; i < t->fwd.size(); ++i) {
+    const FwdItem& f = t->fwd[i];
+    int64_t keys = f.nkv;
+    if (bf16) {
+      const int u0 = f.head0 % s.g / s.hc * 8;
+      if (u0 / s.g * Q_SUB >= f.nq) continue;
+      const int last = std::min<int>(f.nq, ((u0 + 7) / s.g + 1) * Q_SUB) - 1;
+      keys = std::max<int64_t>(1, std::min<int64_t>(f.nkv, (int64_t)t->row_pos[t->q_list[f.q_off + last]] + 1 - f.kv_pos0));
+    }
+    launch.push_back({(keys + KV_TILE - 1) / KV_TILE, (int)i});
+  }
+  std::stable_sort(launch.begin(), launch.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  std::vector<FwdItem> fwd_launch;
+  for (const auto& l : launch) fwd_launch.push_back(t->fwd[l.second]);
+  t->n_fwd_launch = (int32_t)fwd_launch.size();
   std::vector<BkvItem> bkv_launch;
 
   // ---------------- dK/dV tasks: key tile x consumer-row chunk ----------------
@@ -846,7 +862,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   put(t->o_qpos, &past_list, 4);
   put(t->o_qpos + 4, t->q_pos.data(), t->q_pos.size() * 4);
   put(t->o_kv, t->kv_list.data(), t->kv_list.size() * 4);
-  put(t->o_fwd, fwd_launch.data(), t->fwd.size() * sizeof(FwdItem));
+  put(t->o_fwd, fwd_launch.data(), fwd_launch.size() * sizeof(FwdItem));
   put(t->o_merge, t->merge.data(), t->merge.size() * sizeof(MergeEntry));
   put(t->o_bkv, bkv_launch.data(), t->bkv.size() * sizeof(BkvItem));
   put(t->o_reduce, t->reduce.data(), t->reduce.size() * sizeof(ReduceEntry));
@@ -1037,7 +1053,7 @@ psattn_status psattn_fwd(const psattn_tree* t, const void* Q, const void* K, con
   FwdArgs a;
   a.plan = plan_view(t);
   a.s = t->shape;
-  a.n_items = (int32_t)t->fwd.size();
+  a.n_items = t->n_fwd_launch;
   a.n_merge = (int32_t)t->merge.size();
   a.max_merge_rows = t->max_merge_rows;
   a.Q = Q;
@@ -1073,7 +1089,7 @@ psattn_status psattn_bwd(const psattn_tree* t, const void* Q, const void* K, con
   BwdArgs a;
   a.plan = plan_view(t);
   a.s = t->shape;
-  a.n_fwd = (int32_t)t->fwd.size();
+  a.n_fwd = t->n_fwd_launch;
   a.n_merge = (int32_t)t->merge.size();
   a.max_merge_rows = t->max_merge_rows;
   a.n_bkv = (int32_t)t->bkv.size();

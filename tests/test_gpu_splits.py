@@ -20,3 +20,15 @@ def test_merge_of_many_pieces(d, keys, dtype):
     wl = W.custom([-1, 0, 0], [keys - 10, 33, 9], [1, 2], hq=2, hkv=1, d=d, dtype=dtype, seed=71)
     print(f"merge d={d} keys={keys} {dtype}", file=sys.stderr, flush=True)
     H.check_full(wl, H.run_gpu(wl, opts={"fwd_kv_split": 64, "bwd_q_chunk": 32}), H.run_oracle(wl))
+
+
+# 8 (subtile, head) units per forward / dQ item, subtile by subtile, for group sizes that do and do not
+# divide 8: rows just below, at and above 32-row subtiles, tiles whose last items have no rows, split
+# ranges whose first rows see none of a later piece, and packed siblings
+@pytest.mark.parametrize("opts", [None, {"fwd_kv_split": 64, "bwd_q_chunk": 64}])
+@pytest.mark.parametrize("hq,hkv,d", [(3, 1, 128), (5, 1, 64), (12, 2, 128), (7, 1, 64), (8, 1, 128), (16, 1, 64)])
+def test_items_of_every_group_size(hq, hkv, d, opts):
+    wl = W.custom([-1, 0, 0, 1, 0, 0, 0], [161, 33, 130, 64, 7, 12, 1], [2, 3, 4, 5, 6], hq=hq, hkv=hkv, d=d, dtype="bf16",
+                  seed=72)
+    print(f"units hq={hq} hkv={hkv} d={d} {opts}", file=sys.stderr, flush=True)
+    H.check_full(wl, H.run_gpu(wl, opts=opts), H.run_oracle(wl))
