@@ -342,6 +342,10 @@ psattn_status psattn_tree_get_info(const psattn_tree* tree, psattn_tree_info* in
  *   7 pad_slots [n]           pool slots that hold no token
  *   8 row_slot [Ns]           pool slot of each packed row's K/V
  *   9 q_pos                   sequence position of each q_list entry
+ *  10 fwd_launch [n][8]       the forward items as launched, in launch order: those with rows; packed
+ *                             siblings on an unsplit prefix as one item (part -2) of the prefix's keys
+ *                             and then the siblings' own, in the order of its rows
+ *  11 merge_launch [n][4]     the merge records that the launched items need
  * *data stays valid until psattn_tree_destroy. */
 psattn_status psattn_tree_plan_array(const psattn_tree* tree, int which, const int32_t** data,
                                      int64_t* count, int32_t* width);

@@ -640,7 +640,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // issues the S = K Q^T and dP = V dO^T MFMAs of 32-key block j+1 and the dQ^T += K^T dS^T MFMAs
 // of block j-1, and between them computes P = exp2(S c - LSE log2 e) and dS = P (dP - Delta) of
 // block j.
-template <int D, int NW, int NS, int NH>
+template <int D, int NW, int NS, int NH, bool SIB>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH, 3 - NH))) void bwd_dq_bf16_w64_kernel(BwdArgs a) {
   constexpr int RB = D * 2;
   constexpr int CPR = D / 8;
@@ -662,7 +662,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const ItemUnits un = item_units(a.s, a.plan, it);
+  const ItemUnits un = item_units<SIB>(a.s, a.plan, it);
   const int hk = un.hk;
   const int nkv = un.nkv;
   const int* kvl = a.plan.kv_list + it.kv_off;
@@ -674,6 +674,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   }
 
   int ridx[NH], row[NH], lim[NH], head[NH];
+  uint32_t gap[NH];   // packed siblings: the first gap of their own keys belong to earlier siblings
   bool row_ok[NH];
   float lse2[NH], del[NH];
   // sum over this lane's keys of dS' = P (dP - Delta), with Delta = dO . O from the bf16 O: the
@@ -685,8 +686,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     const int st = un.subtile(a.s, wave * NH + rh, head[rh]);
     ridx[rh] = 32 * st + l32;
     row_ok[rh] = ridx[rh] < it.nq;
-    row[rh] = a.plan.q_list[it.q_off + (row_ok[rh] ? ridx[rh] : it.nq - 1)];
-    lim[rh] = min(nkv - 1, a.plan.row_pos[row[rh]] - it.kv_pos0);
+    const int r = row_ok[rh] ? ridx[rh] : it.nq - 1;
+    row[rh] = a.plan.q_list[it.q_off + r];
+    const RowKeys rk = row_keys<SIB>(it, nkv, r, a.plan.q_pos[it.q_off + r]);
+    lim[rh] = rk.lim;
+    gap[rh] = rk.gap;
     lse2[rh] = a.lse2[(size_t)row[rh] * a.s.hq + head[rh]];
     del[rh] = a.delta[(size_t)row[rh] * a.s.hq + head[rh]];
     const size_t o = ((size_t)row[rh] * a.s.hq + head[rh]) * D + 8 * hh;
@@ -779,11 +783,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     const int x = lim[rh] - kb - 4 * hh;    // element v holds key kb + 4*hh + 8*(v/4) + v%4
     S[rh][v] = (8 * (v >> 2) + (v & 3) > x) ? kNegInf : S[rh][v];
   };
+  // packed siblings: the keys of earlier siblings, hidden before the stage (a wave-uniform branch in
+  // the kernels of plans that have such items; the scores' MFMAs may still be in flight)
+  auto mask_siblings = [&](f32x16 (&S)[NH], int kb) __attribute__((always_inline)) {
+    if (!SIB || it.part != PART_SIBLINGS) return;
+    mfma_fence();
+    const int y = kb + 4 * hh - (it.nkv - it.nq);
+#pragma unroll
+    for (int rh = 0; rh < NH; ++rh) {
+      pin_v(S[rh]);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) S[rh][v] = (uint32_t)(8 * (v >> 2) + (v & 3) + y) < gap[rh] ? kNegInf : S[rh][v];
+    }
+  };
   // ---- one stage.  Sc, dPc: block j (dS now); Sn, dPn: block j+1 (MFMAs now, K and V rows at
   // Kn, Vn); dSp: dS of block j-1 (dQ MFMAs now, K rows at Kp); dSc: block j's dS (written).
   auto stage = [&](f32x16 (&Sc)[NH], f32x16 (&dPc)[NH], f32x16 (&Sn)[NH], f32x16 (&dPn)[NH],
                    const bf16x8 (&dSp)[NH][2], bf16x8 (&dSc)[NH][2], const uint8_t* Kn, const uint8_t* Vn,
                    const uint8_t* Kp, int kb, auto masked, auto extra, auto dq_first) __attribute__((always_inline)) {
+    if constexpr (decltype(masked)::value) mask_siblings(Sc, kb);
     // element e = 16 rh + v: scaled and shifted at chunk F(e), exponentiated at F(e)+1,
     // multiplied by dP - Delta at F(e)+2; each 8-element group is packed after its last product
     auto F = [](int e) constexpr { return (e * 29) / (16 * NH); };
@@ -1188,14 +1206,20 @@ hipError_t launch_bwd_kv(const BwdArgs& a, bool bf16, hipStream_t st) {
 }
 
 hipError_t launch_bwd_dq(const BwdArgs& a, bool bf16, hipStream_t st) {
+  using dev::Flag;
   const dim3 grid(a.n_fwd);
   if (bf16) {
     // 8 / NH waves of NH*32 rows (the planner makes every item 8 (subtile, head) pairs)
     if (a.s.nw != 8) return hipErrorInvalidValue;
     constexpr int NW = 8 / PSATTN_DQ_NH;
     const dim3 block(NW * 64);
-    if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<128, NW, 4, PSATTN_DQ_NH>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<64, NW, 4, PSATTN_DQ_NH>), grid, block, 0, st, a);
+    auto launch = [&](auto sib) {   // SIB: as the forward kernel's
+      constexpr bool SIB = decltype(sib)::value;
+      if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<128, NW, 4, PSATTN_DQ_NH, SIB>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((bwd_dq_bf16_w64_kernel<64, NW, 4, PSATTN_DQ_NH, SIB>), grid, block, 0, st, a);
+    };
+    if (a.siblings) launch(Flag<true>{});
+    else launch(Flag<false>{});
   } else {
     return launch_bwd_dq_f32(a, st);
   }

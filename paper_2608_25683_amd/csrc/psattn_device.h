@@ -291,16 +291,35 @@ struct ItemUnits {
     return st;
   }
 };
+template <bool SIB>
 __device__ __forceinline__ ItemUnits item_units(const Shape& s, const PlanView& plan, const FwdItem& it) {
   ItemUnits u;
   u.hk = it.head0 / s.g;
   u.u0 = (it.head0 - u.hk * s.g) / s.hc * 8;
   const int r0 = u.u0 / s.g * 32, r1 = min(it.nq, ((u.u0 + 7) / s.g + 1) * 32) - 1;   // first and last row
-  // a tile's rows have ascending positions, or all lie past the range (packed siblings)
+  if (SIB && it.part == PART_SIBLINGS) {
+    u.nkv = it.nkv - it.nq + r1 + 1;
+    u.nfull = (it.nkv - it.nq) / KV_TILE;
+    return u;
+  }
+  // a tile's rows have ascending positions, or all lie past the range (packed siblings' prefix)
   const int* pos = plan.q_pos + it.q_off;
   u.nkv = max(1, min(it.nkv, pos[r1] + 1 - it.kv_pos0));
   u.nfull = max(0, min(u.nkv, pos[r0] + 1 - it.kv_pos0)) / KV_TILE;
   return u;
+}
+
+// The keys of an item that row ridx (position qpos) sees: key k iff k <= lim and not pre <= k < pre + gap,
+// with pre = nkv - nq: in an item of packed siblings, the earlier siblings' own keys (else gap = 0).
+struct RowKeys {
+  int lim;
+  uint32_t gap;
+};
+template <bool SIB>
+__device__ __forceinline__ RowKeys row_keys(const FwdItem& it, int nkv, int ridx, int qpos) {
+  if (!SIB || it.part != PART_SIBLINGS) return {min(nkv - 1, qpos - it.kv_pos0), 0u};
+  const int pre = it.nkv - it.nq;
+  return {pre + ridx, (uint32_t)(ridx - (qpos - pre))};
 }
 
 }  // namespace dev

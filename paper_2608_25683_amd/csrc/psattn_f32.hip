@@ -95,7 +95,7 @@ __device__ __forceinline__ void put_tile(float* tile, const f32x16 (&acc)[D / 32
 
 // ============================================================================================
 // Forward: one FwdItem of up to 32 rows x one head; wave w takes the 32-key blocks w, w + 4, ...
-template <int D>
+template <int D, bool SIB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128 ? 1 : 2))) void fwd_f32_kernel(FwdArgs a) {
   typedef typename Ops<D>::vec vec;
   constexpr int DB = D / 32, LS = Ops<D>::LS;
@@ -105,8 +105,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int head = it.head0, hk = head / a.s.g;
-  const int row = a.plan.q_list[it.q_off + min(l32, it.nq - 1)];
-  const int lim = min(it.nkv - 1, a.plan.row_pos[row] - it.kv_pos0);
+  const int ridx = min(l32, it.nq - 1), row = a.plan.q_list[it.q_off + ridx];
+  const RowKeys rk = row_keys<SIB>(it, it.nkv, ridx, a.plan.q_pos[it.q_off + ridx]);
+  auto hidden = [&](int k) { return k > rk.lim || (SIB && (uint32_t)(k - (it.nkv - it.nq)) < rk.gap); };
   const size_t kv_stride = (size_t)a.s.hkv * D;
   const int* kvl = a.plan.kv_list + it.kv_off;
   const float* Kh = (const float*)a.K + (size_t)hk * D;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128
     float mx = kNegInf;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      s[e] = 32 * b + res_row(e, hh) > lim ? kNegInf : s[e] * a.s.scale;
+      s[e] = hidden(32 * b + res_row(e, hh)) ? kNegInf : s[e] * a.s.scale;
       mx = fmaxf(mx, s[e]);
     }
     const float m_new = fmaxf(m_run, pair_max(mx));
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128
 
 // ============================================================================================
 // dQ: the forward's items and split; dQ^T += K^T dS^T with dS = P (dO V^T - Delta)
-template <int D>
+template <int D, bool SIB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_dq_f32_kernel(BwdArgs a) {
   typedef typename Ops<D>::vec vec;
   constexpr int DB = D / 32, LS = Ops<D>::LS;
@@ -205,8 +206,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int head = it.head0, hk = head / a.s.g;
-  const int row = a.plan.q_list[it.q_off + min(l32, it.nq - 1)];
-  const int lim = min(it.nkv - 1, a.plan.row_pos[row] - it.kv_pos0);
+  const int ridx = min(l32, it.nq - 1), row = a.plan.q_list[it.q_off + ridx];
+  const RowKeys rk = row_keys<SIB>(it, it.nkv, ridx, a.plan.q_pos[it.q_off + ridx]);
+  auto hidden = [&](int k) { return k > rk.lim || (SIB && (uint32_t)(k - (it.nkv - it.nq)) < rk.gap); };
   const float lse = a.LSE[(size_t)head * a.s.ns + row];
   const float del = a.delta[(size_t)row * a.s.hq + head];
   const size_t kv_stride = (size_t)a.s.hkv * D;
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     sched_fence();
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const float p = 32 * b + res_row(e, hh) > lim ? 0.f : expf(s[e] * a.s.scale - lse);
+      const float p = hidden(32 * b + res_row(e, hh)) ? 0.f : expf(s[e] * a.s.scale - lse);
       s[e] = p * (dp[e] - del);
     }
     acc_rows<D>(dq, kt, s);
@@ -390,15 +392,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // One workgroup per item (the planner makes fp32 items 32 rows x one head)
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t st) {
   if (a.s.bmq != 32 || a.s.hc != 1) return hipErrorInvalidValue;
-  if (a.s.d == 128) hipLaunchKernelGGL((fwd_f32_kernel<128>), dim3(a.n_items), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((fwd_f32_kernel<64>), dim3(a.n_items), dim3(256), 0, st, a);
+  auto launch = [&](auto sib) {   // SIB: plans with items of packed siblings
+    constexpr bool SIB = decltype(sib)::value;
+    if (a.s.d == 128) hipLaunchKernelGGL((fwd_f32_kernel<128, SIB>), dim3(a.n_items), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((fwd_f32_kernel<64, SIB>), dim3(a.n_items), dim3(256), 0, st, a);
+  };
+  if (a.siblings) launch(dev::Flag<true>{});
+  else launch(dev::Flag<false>{});
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_dq_f32(const BwdArgs& a, hipStream_t st) {
   if (a.s.bmq != 32 || a.s.hc != 1) return hipErrorInvalidValue;
-  if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_f32_kernel<128>), dim3(a.n_fwd), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((bwd_dq_f32_kernel<64>), dim3(a.n_fwd), dim3(256), 0, st, a);
+  auto launch = [&](auto sib) {   // SIB: plans with items of packed siblings
+    constexpr bool SIB = decltype(sib)::value;
+    if (a.s.d == 128) hipLaunchKernelGGL((bwd_dq_f32_kernel<128, SIB>), dim3(a.n_fwd), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((bwd_dq_f32_kernel<64, SIB>), dim3(a.n_fwd), dim3(256), 0, st, a);
+  };
+  if (a.siblings) launch(dev::Flag<true>{});
+  else launch(dev::Flag<false>{});
   return hipGetLastError();
 }
 

@@ -42,7 +42,7 @@ using namespace dev;
 // block j-1, and between them the softmax of block j (its scores were finished during stage
 // j-1).  The instruction order inside a stage is fixed (scheduling fences).  Key tiles (two
 // blocks) come through an NS-stage LDS ring, one barrier per tile.
-template <int D, int NW, int NS, int NH>
+template <int D, int NW, int NS, int NH, bool SIB>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH, 3 - NH))) void fwd_bf16_w64_kernel(FwdArgs a) {
   constexpr int RB = D * 2;
   constexpr int CPR = D / 8;
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const ItemUnits un = item_units(a.s, a.plan, it);
+  const ItemUnits un = item_units<SIB>(a.s, a.plan, it);
   const int hk = un.hk;
   const int nkv = un.nkv;
   const int* kvl = a.plan.kv_list + it.kv_off;
@@ -75,6 +75,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   }
 
   int ridx[NH], row[NH], lim[NH], head[NH];
+  uint32_t gap[NH];   // packed siblings: the first gap of their own keys belong to earlier siblings
   bool row_ok[NH];
   bf16x8 qreg[NH][KS];
 #pragma unroll
@@ -82,9 +83,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     const int st = un.subtile(a.s, wave * NH + rh, head[rh]);
     ridx[rh] = 32 * st + l32;
     row_ok[rh] = ridx[rh] < it.nq;
-    row[rh] = a.plan.q_list[it.q_off + (row_ok[rh] ? ridx[rh] : it.nq - 1)];
-    // key kidx of this item is visible to the row iff kidx <= lim
-    lim[rh] = min(nkv - 1, a.plan.row_pos[row[rh]] - it.kv_pos0);
+    const int r = row_ok[rh] ? ridx[rh] : it.nq - 1;
+    row[rh] = a.plan.q_list[it.q_off + r];
+    const RowKeys rk = row_keys<SIB>(it, nkv, r, a.plan.q_pos[it.q_off + r]);
+    lim[rh] = rk.lim;
+    gap[rh] = rk.gap;
     const bf16_t* qp = (const bf16_t*)a.Q + ((size_t)row[rh] * a.s.hq + head[rh]) * D + 8 * hh;
 #pragma unroll
     for (int s = 0; s < KS; ++s) qreg[rh][s] = as_bf(ld16(qp + 16 * s));
@@ -192,9 +195,23 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     const int x = lim[rh] - kb - 4 * hh;
     S[rh][v] = (8 * (v >> 2) + (v & 3) > x) ? kNegInf : S[rh][v];
   };
+  // packed siblings: the keys of earlier siblings, hidden before the stage (a wave-uniform branch in
+  // the kernels of plans that have such items; the scores' MFMAs may still be in flight)
+  auto mask_siblings = [&](f32x16 (&S)[NH], int kb) __attribute__((always_inline)) {
+    if (!SIB || it.part != PART_SIBLINGS) return;
+    mfma_fence();
+    const int y = kb + 4 * hh - (it.nkv - it.nq);
+#pragma unroll
+    for (int rh = 0; rh < NH; ++rh) {
+      pin_v(S[rh]);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) S[rh][v] = (uint32_t)(8 * (v >> 2) + (v & 3) + y) < gap[rh] ? kNegInf : S[rh][v];
+    }
+  };
   auto stage = [&](f32x16 (&Sc)[NH], f32x16 (&Sn)[NH], const bf16x8 (&Pp)[NH][2], bf16x8 (&Pc)[NH][2],
                    const uint8_t* Kc, const uint8_t* Kn, const uint8_t* Vp, int kb, auto masked,
                    auto extra, auto pv_first) __attribute__((always_inline)) {
+    if constexpr (decltype(masked)::value) mask_siblings(Sc, kb);
     float mx[NH], mt[NH], ps[NH][2], l_prev[NH], mc[NH];
     bool g[NH];
 #pragma unroll
@@ -307,6 +324,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
       // exponentiate them against the new maxima, and rescale O and the running sums.
       f32x16 R[NH];
       scores(Kc, R);
+      if constexpr (decltype(masked)::value) mask_siblings(R, kb);
       mfma_fence();
 #pragma unroll
       for (int rh = 0; rh < NH; ++rh) {
@@ -539,14 +557,22 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
 }  // namespace
 
 hipError_t launch_fwd_main(const FwdArgs& a, bool bf16, hipStream_t st) {
+  using dev::Flag;
   const dim3 grid(a.n_items);
   if (bf16) {
     // 8 / NH waves of NH*32 rows (the planner makes every item 8 (subtile, head) pairs); the pools
     // are addressed by 32-bit byte offsets (the host rejects larger trees)
     if (a.s.nw != 8) return hipErrorInvalidValue;
-    const dim3 block(8 / PSATTN_FWD_NH * 64);
-    if (a.s.d == 128) hipLaunchKernelGGL((fwd_bf16_w64_kernel<128, 8 / PSATTN_FWD_NH, PSATTN_FWD_NS, PSATTN_FWD_NH>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd_bf16_w64_kernel<64, 8 / PSATTN_FWD_NH, PSATTN_FWD_NS, PSATTN_FWD_NH>), grid, block, 0, st, a);
+    constexpr int NW = 8 / PSATTN_FWD_NH;
+    const dim3 block(NW * 64);
+    // SIB: plans with items of packed siblings (their mask costs every masked tile of the others 1%)
+    auto launch = [&](auto sib) {
+      constexpr bool SIB = decltype(sib)::value;
+      if (a.s.d == 128) hipLaunchKernelGGL((fwd_bf16_w64_kernel<128, NW, PSATTN_FWD_NS, PSATTN_FWD_NH, SIB>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((fwd_bf16_w64_kernel<64, NW, PSATTN_FWD_NS, PSATTN_FWD_NH, SIB>), grid, block, 0, st, a);
+    };
+    if (a.siblings) launch(Flag<true>{});
+    else launch(Flag<false>{});
   } else {
     return launch_fwd_f32(a, st);
   }

@@ -67,8 +67,10 @@ struct psattn_tree {
   std::vector<BkvItem> bkv;
   std::vector<ReduceEntry> reduce;
   int64_t fwd_part_rows = 0, bkv_part_tiles = 0;
-  int32_t max_merge_rows = 0;
-  int32_t n_fwd_launch = 0;   // forward / dQ items in the device image (those with rows)
+  int32_t max_merge_rows = 0, siblings = 0;
+  // the forward / dQ items and merge records of the device image (see build_plan)
+  std::vector<FwdItem> fwd_launch;
+  std::vector<MergeEntry> merge_launch;
   // device image of the plan
   size_t o_row_pos = 0, o_row_slot = 0, o_q = 0, o_qpos = 0, o_kv = 0, o_fwd = 0, o_merge = 0, o_bkv = 0, o_reduce = 0, o_pad = 0;
   size_t plan_bytes = 0;
@@ -317,6 +319,14 @@ psattn_status check_plan(const psattn_tree* t) {
     if (f.part < -1 || (f.part >= 0 && (int64_t)f.part + f.nq > t->fwd_part_rows)) return bad("forward item partial rows", (int64_t)i);
     if (f.nfull < 0 || (int64_t)f.nfull * KV_TILE > f.nkv + KV_TILE - 1) return bad("forward item unmasked tiles", (int64_t)i);
   }
+  for (size_t i = 0; i < t->fwd_launch.size(); ++i) {
+    const FwdItem& f = t->fwd_launch[i];
+    if (f.nq < 1 || f.nq > s.bmq || f.q_off < 0 || (int64_t)f.q_off + f.nq > nql) return bad("launched item rows", (int64_t)i);
+    if (f.nkv < 1 || f.kv_off < 0 || (int64_t)f.kv_off + f.nkv > nkl) return bad("launched item keys", (int64_t)i);
+    if (f.head0 < 0 || f.head0 + s.hc > s.hq) return bad("launched item heads", (int64_t)i);
+    if (f.part < PART_SIBLINGS || (f.part >= 0 && (int64_t)f.part + f.nq > t->fwd_part_rows)) return bad("launched item partial rows", (int64_t)i);
+    if (f.part == PART_SIBLINGS && f.nkv < f.nq) return bad("launched sibling keys", (int64_t)i);
+  }
   for (size_t i = 0; i < t->merge.size(); ++i) {
     const MergeEntry& m = t->merge[i];
     if (m.nq < 1 || m.q_off < 0 || (int64_t)m.q_off + m.nq > nql) return bad("merge rows", (int64_t)i);
@@ -400,7 +410,10 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // order) into one tile for that range, and each node keeps an item of its own keys
   // [off, off + seg).  A pack's partial rows: prefix piece j of the node at pack offset o at
   // P + j*bmq + o, the node's own piece at P + npref*bmq + o, so that one merge record per node
-  // (part0 = P + o, npref + 1 parts) combines them.
+  // (part0 = P + o, npref + 1 parts) combines them.  (An unsplit prefix, npref = 1, is launched with the
+  // siblings' own keys behind it as one item that writes its results directly: no partial rows, and no
+  // item start-up per sibling for its few own keys.  256 branches of 16 rows on a 4096-token prompt, 32/8
+  // heads: forward + merge 507 -> 388 us, dQ + sum 636 -> 518 us.)
   std::vector<char> packed(N, 0);
   std::vector<std::vector<int>> packs;
   for (int p = 0; p < N; ++p) {
@@ -483,15 +496,10 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     // merge passes; a long range on an idle chip costs more (a 4096-token cached prefix and 48 new
     // rows: 218 us whole).
     std::vector<std::pair<int64_t, int>> ranges;   // (keys, rows) of every splittable range
-    std::vector<double> fixed;
     int64_t rows0 = 0;                             // partial rows there are in any case
-    for (const std::vector<int>& pk : packs) {
-      int rows = 0;
-      for (int n : pk) {
-        rows += t->seg_len[n];
-        fixed.push_back(ic.fwd0 + ic.fwd_tile * (double)((t->seg_len[n] + KV_TILE - 1) / KV_TILE));
-      }
-      ranges.push_back({t->off[pk[0]], rows});
+    std::vector<int> pack_rows(packs.size(), 0);
+    for (size_t i = 0; i < packs.size(); ++i) {
+      for (int n : packs[i]) pack_rows[i] += t->seg_len[n];
       rows0 += 2 * s.bmq;
     }
     for (int n = 0; n < N; ++n)
@@ -504,9 +512,22 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     int64_t best_cap = INT64_MAX;
     for (int64_t cap : {INT64_MAX, (int64_t)32, (int64_t)24, (int64_t)16, (int64_t)12, (int64_t)8, (int64_t)6, (int64_t)4}) {
       cap_tiles = cap;
-      std::vector<double> c = fixed;
+      std::vector<double> c;
       double moved = 0.0;
       int64_t prows = rows0;
+      for (size_t i = 0; i < packs.size(); ++i) {
+        const int64_t pre = t->off[packs[i][0]], k = piece_keys(pre);
+        const int n = num_pieces(pre);
+        if (n == 1) {   // one item, its siblings' own keys after the prefix
+          c.push_back(ic.fwd0 + ic.fwd_tile * (double)((pre + pack_rows[i] + KV_TILE - 1) / KV_TILE));
+          continue;
+        }
+        for (int j = 0; j < n; ++j)
+          c.push_back(ic.fwd0 + ic.fwd_tile * (double)((std::min(k, pre - j * k) + KV_TILE - 1) / KV_TILE));
+        for (int m : packs[i]) c.push_back(ic.fwd0 + ic.fwd_tile * (double)((t->seg_len[m] + KV_TILE - 1) / KV_TILE));
+        moved += 4.0 * (n + 1) * pack_rows[i] * t->hq * t->d * 4.0;
+        prows += (int64_t)(n - 1) * s.bmq;
+      }
       for (const auto& r : ranges) {
         const int n = num_pieces(r.first);
         const int64_t k = piece_keys(r.first);
@@ -519,7 +540,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       }
       if (c.size() > 65536) break;
       if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(rows0, base_tiles) <= kNoallocBytes) break;
-      const double time = makespan(c, (double)num_cus / n_chunks) + (moved > 0 && packs.empty() ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
+      const double time = makespan(c, (double)num_cus / n_chunks) + (moved > 0 ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
       if (cap == INT64_MAX || time < kSplitGain * best) {
         best = time;
         best_cap = cap;
@@ -527,6 +548,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     }
     cap_tiles = best_cap;
   }
+  std::vector<FwdItem> sib_items;   // the launched items of unsplit packs (head0 per chunk)
+  std::vector<int32_t> sib_part;    // and the first partial row of the items and merges they replace
   for (const std::vector<int>& pk : packs) {
     const int n0 = pk[0];
     const int64_t pre = t->off[n0];   // the common prefix: every sibling starts at the same position
@@ -551,6 +574,16 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       f.part = P + j * s.bmq;
       f.cost = (double)f.nq * (double)f.nkv + 4096.0;
       ftasks.push_back(f);
+    }
+    if (npref == 1) {
+      // launched as one item: the prefix's keys, then the siblings' own (PART_SIBLINGS)
+      const int32_t nq = (int32_t)t->q_list.size() - q_pack;
+      sib_items.push_back({q_pack, nq, (int32_t)t->kv_list.size(), (int32_t)(pre + nq), 0, 0, PART_SIBLINGS, (int32_t)(pre / KV_TILE)});
+      const std::vector<int32_t> prefix(t->kv_list.begin() + kvoff[n0], t->kv_list.begin() + kvoff[n0] + pre);
+      t->kv_list.insert(t->kv_list.end(), prefix.begin(), prefix.end());
+      for (int n : pk) t->kv_list.insert(t->kv_list.end(), node_slots[n].begin(), node_slots[n].end());
+      if (t->kv_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "key lists exceed 2^31 entries");
+      sib_part.push_back(P);
     }
     for (int n : pk) {
       const int32_t q_off = (int32_t)t->q_list.size();
@@ -605,8 +638,6 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   if (part_rows > INT32_MAX / 2) return fail(PSATTN_E_UNSUPPORTED, "too many partial rows");
   t->fwd_part_rows = part_rows;
   t->merge = merges;
-  t->max_merge_rows = 0;
-  for (const MergeEntry& m : merges) t->max_merge_rows = std::max(t->max_merge_rows, m.nq);
   {
     std::vector<double> c(ftasks.size());
     for (size_t i = 0; i < ftasks.size(); ++i) c[i] = ftasks[i].cost;
@@ -634,22 +665,40 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // bf16 items hold 8 (subtile, head) units of their tile, subtile by subtile (item_units in the
   // kernels): an item's keys end at its last row, and one whose units all lie past the tile's last row
   // is not launched.
+  t->siblings = !sib_items.empty();
+  std::vector<char> replaced(part_rows / s.bmq + 1, 0);   // by groups of bmq partial rows
+  for (int32_t P : sib_part) replaced[P / s.bmq] = replaced[P / s.bmq + 1] = 1;
+  std::vector<FwdItem> items;
+  for (const FwdItem& f : t->fwd)
+    if (f.part < 0 || !replaced[f.part / s.bmq]) items.push_back(f);
+  for (const FwdItem& f : sib_items)
+    for (int j = 0; j < n_chunks; ++j) {
+      items.push_back(f);
+      items.back().head0 = j % t->hkv * s.g + j / t->hkv * s.hc;
+    }
   std::vector<std::pair<int64_t, int>> launch;   // (key tiles, item)
-  for (size_t i = 0; i < t->fwd.size(); ++i) {
-    const FwdItem& f = t->fwd[i];
+  for (size_t i = 0; i < items.size(); ++i) {
+    const FwdItem& f = items[i];
     int64_t keys = f.nkv;
     if (bf16) {
       const int u0 = f.head0 % s.g / s.hc * 8;
       if (u0 / s.g * Q_SUB >= f.nq) continue;
       const int last = std::min<int>(f.nq, ((u0 + 7) / s.g + 1) * Q_SUB) - 1;
-      keys = std::max<int64_t>(1, std::min<int64_t>(f.nkv, (int64_t)t->row_pos[t->q_list[f.q_off + last]] + 1 - f.kv_pos0));
+      if (f.part == PART_SIBLINGS) keys = f.nkv - f.nq + last + 1;
+      else keys = std::max<int64_t>(1, std::min<int64_t>(f.nkv, (int64_t)t->row_pos[t->q_list[f.q_off + last]] + 1 - f.kv_pos0));
     }
     launch.push_back({(keys + KV_TILE - 1) / KV_TILE, (int)i});
   }
   std::stable_sort(launch.begin(), launch.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-  std::vector<FwdItem> fwd_launch;
-  for (const auto& l : launch) fwd_launch.push_back(t->fwd[l.second]);
-  t->n_fwd_launch = (int32_t)fwd_launch.size();
+  t->fwd_launch.clear();
+  for (const auto& l : launch) t->fwd_launch.push_back(items[l.second]);
+  t->merge_launch.clear();
+  t->max_merge_rows = 0;
+  for (const MergeEntry& m : t->merge) {
+    if (replaced[m.part0 / s.bmq]) continue;
+    t->merge_launch.push_back(m);
+    t->max_merge_rows = std::max(t->max_merge_rows, m.nq);
+  }
   std::vector<BkvItem> bkv_launch;
 
   // ---------------- dK/dV tasks: key tile x consumer-row chunk ----------------
@@ -846,8 +895,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   t->o_q = place(t->q_list.size() * 4);
   t->o_qpos = place((t->q_pos.size() + 1) * 4);
   t->o_kv = place(t->kv_list.size() * 4);
-  t->o_fwd = place(t->fwd.size() * sizeof(FwdItem));
-  t->o_merge = place(t->merge.size() * sizeof(MergeEntry));
+  t->o_fwd = place(t->fwd_launch.size() * sizeof(FwdItem));
+  t->o_merge = place(t->merge_launch.size() * sizeof(MergeEntry));
   t->o_bkv = place(t->bkv.size() * sizeof(BkvItem));
   t->o_reduce = place(t->reduce.size() * sizeof(ReduceEntry));
   t->o_pad = place(t->pad_slots.size() * 4);
@@ -862,8 +911,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   put(t->o_qpos, &past_list, 4);
   put(t->o_qpos + 4, t->q_pos.data(), t->q_pos.size() * 4);
   put(t->o_kv, t->kv_list.data(), t->kv_list.size() * 4);
-  put(t->o_fwd, fwd_launch.data(), fwd_launch.size() * sizeof(FwdItem));
-  put(t->o_merge, t->merge.data(), t->merge.size() * sizeof(MergeEntry));
+  put(t->o_fwd, t->fwd_launch.data(), t->fwd_launch.size() * sizeof(FwdItem));
+  put(t->o_merge, t->merge_launch.data(), t->merge_launch.size() * sizeof(MergeEntry));
   put(t->o_bkv, bkv_launch.data(), t->bkv.size() * sizeof(BkvItem));
   put(t->o_reduce, t->reduce.data(), t->reduce.size() * sizeof(ReduceEntry));
   put(t->o_pad, t->pad_slots.data(), t->pad_slots.size() * 4);
@@ -1053,9 +1102,10 @@ psattn_status psattn_fwd(const psattn_tree* t, const void* Q, const void* K, con
   FwdArgs a;
   a.plan = plan_view(t);
   a.s = t->shape;
-  a.n_items = t->n_fwd_launch;
-  a.n_merge = (int32_t)t->merge.size();
+  a.n_items = (int32_t)t->fwd_launch.size();
+  a.n_merge = (int32_t)t->merge_launch.size();
   a.max_merge_rows = t->max_merge_rows;
+  a.siblings = t->siblings;
   a.Q = Q;
   a.K = K;
   a.V = V;
@@ -1089,9 +1139,10 @@ psattn_status psattn_bwd(const psattn_tree* t, const void* Q, const void* K, con
   BwdArgs a;
   a.plan = plan_view(t);
   a.s = t->shape;
-  a.n_fwd = t->n_fwd_launch;
-  a.n_merge = (int32_t)t->merge.size();
+  a.n_fwd = (int32_t)t->fwd_launch.size();
+  a.n_merge = (int32_t)t->merge_launch.size();
   a.max_merge_rows = t->max_merge_rows;
+  a.siblings = t->siblings;
   a.n_bkv = (int32_t)t->bkv.size();
   a.n_reduce = (int32_t)t->reduce.size();
   a.n_pad = (int32_t)t->pad_slots.size();
@@ -1208,6 +1259,8 @@ psattn_status psattn_tree_plan_array(const psattn_tree* t, int which, const int3
     case 7: *data = t->pad_slots.data(); *count = (int64_t)t->pad_slots.size(); *width = 1; break;
     case 8: *data = t->row_slot.data(); *count = (int64_t)t->row_slot.size(); *width = 1; break;
     case 9: *data = t->q_pos.data(); *count = (int64_t)t->q_pos.size(); *width = 1; break;
+    case 10: *data = (const int32_t*)t->fwd_launch.data(); *count = (int64_t)t->fwd_launch.size(); *width = 8; break;
+    case 11: *data = (const int32_t*)t->merge_launch.data(); *count = (int64_t)t->merge_launch.size(); *width = 4; break;
     default: return fail(PSATTN_E_INVALID_ARG, "unknown plan array %d", which);
   }
   return PSATTN_OK;

@@ -11,6 +11,7 @@ struct FwdArgs {
   Shape s;
   int32_t n_items, n_merge;
   int32_t max_merge_rows;   // rows of the largest merge record
+  int32_t siblings;         // the plan has items of packed siblings (PART_SIBLINGS)
   const void* Q;
   const void* K;
   const void* V;
@@ -27,6 +28,7 @@ struct BwdArgs {
   Shape s;
   int32_t n_fwd, n_merge, n_bkv, n_reduce, n_pad;
   int32_t max_merge_rows;   // rows of the largest merge record
+  int32_t siblings;         // the plan has items of packed siblings (PART_SIBLINGS)
   const void* Q;
   const void* K;
   const void* V;

@@ -22,6 +22,11 @@ constexpr int KV_TILE = 64;    // keys per forward / dQ key tile
 constexpr int Q_SUB = 32;      // query rows per wavefront subtile
 constexpr int BKV_TILE = 128;  // keys per dK/dV work item (4 wavefronts x 32 keys)
 
+// part of a launched item of packed siblings: its keys are the nkv - nq keys of the common prefix, then
+// the siblings' own keys in the order of its rows, so that row r's own key is key nkv - nq + r.  A row
+// sees the prefix and its own node's keys up to its own.
+constexpr int32_t PART_SIBLINGS = -2;
+
 struct FwdItem {     // also the dQ item
   int32_t q_off;     // first entry in q_list (packed row indices)
   int32_t nq;        // rows in the tile, 1..q_tile_rows
@@ -29,7 +34,7 @@ struct FwdItem {     // also the dQ item
   int32_t nkv;       // keys in this item's range, >= 1
   int32_t kv_pos0;   // sequence position of the first key
   int32_t head0;     // first query head of the chunk
-  int32_t part;      // -1: write final results; else first partial row
+  int32_t part;      // -1: write final results; PART_SIBLINGS: likewise (below); else first partial row
   int32_t nfull;     // leading key tiles that need no mask
 };
 

@@ -7,7 +7,7 @@ from paper_2608_25683_amd import workloads as W
 
 P = pytest.importorskip("paper_2608_25683_amd.psattn")
 
-from test_abi_host import _check_plan  # noqa: E402
+from test_abi_host import _check_plan, _visible_pairs  # noqa: E402
 
 SHAPES = {   # name -> (parent, seg, samples, hq, hkv): what the automatic rules split
     "long_range": ([-1, 0], [700, 20], [1], 8, 2),            # key ranges of few row tiles
@@ -45,3 +45,51 @@ def test_automatic_splits_stay_within_the_noalloc_array(hq, hkv, prefix, branche
     coarse = P.Tree.from_workload(wl, opts={"fwd_kv_split": -1, "bwd_q_chunk": 1 << 20}).workspace_size(1)
     assert coarse <= limit
     assert P.Tree.from_workload(wl).workspace_size(1) <= limit
+
+
+def _launch_cover(wl, t, bf16):
+    """(head, row, key row) -> times covered, from the launched items as the kernels read them."""
+    G, hc = wl.hq // wl.hkv, t.info["head_chunk"]
+    slot_to_row = {int(s): r for r, s in enumerate(wl.tree.row_slots())}
+    q_list, kv_list, q_pos = t.plan_array("q_list"), t.plan_array("kv_list"), t.plan_array("q_pos")
+    cover, written = {}, set()
+    for q_off, nq, kv_off, nkv, kv_pos0, head0, part, _ in t.plan_array("fwd_launch"):
+        rows, pos = q_list[q_off:q_off + nq], q_pos[q_off:q_off + nq]
+        keys = [slot_to_row[int(s)] for s in kv_list[kv_off:kv_off + nkv]]
+        if bf16:      # 8 (32-row subtile, head) units of the tile, subtile by subtile
+            hk, u0 = head0 // G, head0 % G // hc * 8
+            units = [((u0 + i) // G, hk * G + (u0 + i) % G) for i in range(8)]
+        else:
+            units = [(0, head0)]
+        members = [(h, r) for st, h in units for r in range(32 * st, min(nq, 32 * st + 32))]
+        assert members, "a launched item without rows"
+        for h, r in members:
+            if part != -2:
+                seen = range(min(nkv, pos[r] - kv_pos0 + 1))
+            else:
+                pre = nkv - nq
+                seen = list(range(pre)) + list(range(pre + r - (pos[r] - pre), pre + r + 1))
+            for k in seen:
+                x = (h, int(rows[r]), keys[k])
+                cover[x] = cover.get(x, 0) + 1
+            if part >= 0:
+                assert (part + r, h) not in written
+                written.add((part + r, h))
+    read = {(part0 + j * t.info["q_tile_rows"] + i, h) for _, nq, part0, n in t.plan_array("merge_launch")
+            for j in range(n) for i in range(nq) for h in range(wl.hq)}
+    assert written == read
+    return cover
+
+
+@pytest.mark.parametrize("opts", [{}, {"fwd_kv_split": 64}, {"fwd_kv_split": -1}])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (5, 1), (2, 2), (8, 1), (7, 1), (12, 2)])
+def test_launched_items_cover_the_mask(hq, hkv, dtype, opts):
+    wl = W.custom([-1] + [0] * 7 + [1, 1], [130, 16, 9, 30, 1, 16, 64, 33, 5, 16], list(range(2, 10)), hq=hq, hkv=hkv,
+                  dtype=dtype, tensors=False, block_policy=lambda n: W.blocks_fixed(n, 16))
+    t = P.Tree.from_workload(wl, opts=opts)
+    if opts.get("fwd_kv_split", 0) <= 0:
+        assert (t.plan_array("fwd_launch")[:, 6] == -2).any()
+    cover = _launch_cover(wl, t, dtype == "bf16")
+    assert all(n == 1 for n in cover.values())
+    assert {(r, k) for _, r, k in cover} == _visible_pairs(wl.tree) and len(cover) == len(_visible_pairs(wl.tree)) * hq
