@@ -987,8 +987,8 @@ struct Profiler {
 };
 Profiler g_prof;
 const char* kKernelNames[] = {"fwd_main", "fwd_merge",     "bwd_pre", "bwd_kv",   "bwd_dq", "bwd_reduce_kv",
-                              "bwd_reduce_dq", "bwd_zero_pad", "rope",    "kv_scatter", "kv_gather"};
-constexpr int kNumKernels = 11;
+                              "bwd_reduce_dq", "bwd_zero_pad", "rope",    "kv_scatter", "kv_gather", "split_planes", "silu_bwd"};
+constexpr int kNumKernels = 13;
 
 hipEvent_t get_event() {
   if (!g_prof.spare.empty()) {
@@ -1217,6 +1217,24 @@ psattn_status psattn_kv_gather(const psattn_tree* t, const float* dK, const floa
   return timed(10, st, [&] {
     return launch_kv_move(plan_view(t), (int32_t)t->Ns, row_bytes, false, dK, dV, dK_rows, dV_rows, st);
   });
+}
+
+psattn_status psattn_split_planes(const float* X, void* planes, int64_t n, void* stream) {
+  if (!X || !planes) return fail(PSATTN_E_INVALID_ARG, "NULL argument");
+  if (n < 1) return fail(PSATTN_E_INVALID_ARG, "n must be >= 1 (got %lld)", (long long)n);
+  if (misaligned(X) || misaligned(planes)) return fail(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
+  hipStream_t st = (hipStream_t)stream;
+  return timed(11, st, [&] { return launch_split_planes(X, planes, n, st); });
+}
+
+psattn_status psattn_silu_bwd(const float* dM_planes, const void* A, const void* B, void* dA_planes, void* dB_planes,
+                              int64_t n, void* stream) {
+  if (!dM_planes || !A || !B || !dA_planes || !dB_planes) return fail(PSATTN_E_INVALID_ARG, "NULL argument");
+  if (n < 1) return fail(PSATTN_E_INVALID_ARG, "n must be >= 1 (got %lld)", (long long)n);
+  if (misaligned(dM_planes) || misaligned(A) || misaligned(B) || misaligned(dA_planes) || misaligned(dB_planes))
+    return fail(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
+  hipStream_t st = (hipStream_t)stream;
+  return timed(12, st, [&] { return launch_silu_bwd(dM_planes, A, B, dA_planes, dB_planes, n, st); });
 }
 
 psattn_status psattn_tree_refcounts(const psattn_tree* t, int32_t* node_refcount) {

@@ -69,5 +69,7 @@ hipError_t launch_rope(const PlanView& plan, int32_t ns, int32_t heads, int32_t 
                        void* X, hipStream_t st);
 hipError_t launch_kv_move(const PlanView& plan, int32_t ns, int32_t row_bytes, bool to_pool, const void* a0,
                           const void* a1, void* b0, void* b1, hipStream_t st);
+hipError_t launch_split_planes(const float* x, void* planes, int64_t n, hipStream_t st);
+hipError_t launch_silu_bwd(const float* dm, const void* a, const void* b, void* da, void* db, int64_t n, hipStream_t st);
 
 }  // namespace psattn

@@ -9,7 +9,6 @@
 // fp64 (positions reach 10^4 and beyond), the rotation itself is fp32.
 #include <algorithm>
 
-#include "psattn.h"
 #include "psattn_device.h"
 
 namespace psattn {
@@ -215,44 +214,20 @@ hipError_t launch_kv_move(const PlanView& plan, int32_t ns, int32_t row_bytes, b
   return hipGetLastError();
 }
 
-}  // namespace psattn
-
-// ---------------------------------------------------------------------------------------------
-// C ABI of the steps that need no tree
-
-namespace psattn {
-psattn_status set_error(psattn_status st, const char* msg);
-
 namespace {
-bool misaligned16(const void* p) { return ((uintptr_t)p & 15) != 0; }
-psattn_status launched(const char* what) {
-  const hipError_t e = hipGetLastError();
-  if (e == hipSuccess) return PSATTN_OK;
-  return set_error(PSATTN_E_HIP, what);
-}
 unsigned plane_grid(int64_t n) { return (unsigned)std::min<int64_t>((n % 4 ? n + 255 : n / 4 + 255) / 256, 65536); }
 }  // namespace
+
+hipError_t launch_split_planes(const float* x, void* planes, int64_t n, hipStream_t st) {
+  hipLaunchKernelGGL(n % 4 ? split3_kernel<false> : split3_kernel<true>, dim3(plane_grid(n)), dim3(256), 0, st, x,
+                     (dev::bf16_t*)planes, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_silu_bwd(const float* dm, const void* a, const void* b, void* da, void* db, int64_t n, hipStream_t st) {
+  hipLaunchKernelGGL(n % 4 ? silu_bwd_kernel<false> : silu_bwd_kernel<true>, dim3(plane_grid(n)), dim3(256), 0, st, dm,
+                     (const dev::bf16_t*)a, (const dev::bf16_t*)b, (dev::bf16_t*)da, (dev::bf16_t*)db, n);
+  return hipGetLastError();
+}
+
 }  // namespace psattn
-
-extern "C" psattn_status psattn_split_planes(const float* X, void* planes, int64_t n, void* stream) {
-  using namespace psattn;
-  if (!X || !planes) return set_error(PSATTN_E_INVALID_ARG, "NULL argument");
-  if (n < 1) return set_error(PSATTN_E_INVALID_ARG, "n must be >= 1");
-  if (misaligned16(X) || misaligned16(planes)) return set_error(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
-  hipLaunchKernelGGL(n % 4 ? split3_kernel<false> : split3_kernel<true>, dim3(plane_grid(n)), dim3(256), 0,
-                     (hipStream_t)stream, X, (dev::bf16_t*)planes, n);
-  return launched("split3 launch failed");
-}
-
-extern "C" psattn_status psattn_silu_bwd(const float* dM_planes, const void* A, const void* B, void* dA_planes,
-                                         void* dB_planes, int64_t n, void* stream) {
-  using namespace psattn;
-  if (!dM_planes || !A || !B || !dA_planes || !dB_planes) return set_error(PSATTN_E_INVALID_ARG, "NULL argument");
-  if (n < 1) return set_error(PSATTN_E_INVALID_ARG, "n must be >= 1");
-  if (misaligned16(dM_planes) || misaligned16(A) || misaligned16(B) || misaligned16(dA_planes) || misaligned16(dB_planes))
-    return set_error(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
-  hipLaunchKernelGGL(n % 4 ? silu_bwd_kernel<false> : silu_bwd_kernel<true>, dim3(plane_grid(n)), dim3(256), 0,
-                     (hipStream_t)stream, dM_planes,
-                     (const dev::bf16_t*)A, (const dev::bf16_t*)B, (dev::bf16_t*)dA_planes, (dev::bf16_t*)dB_planes, n);
-  return launched("silu_bwd launch failed");
-}

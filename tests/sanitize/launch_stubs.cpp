@@ -16,4 +16,8 @@ hipError_t launch_rope(const PlanView&, int32_t, int32_t, int32_t, float, bool, 
 hipError_t launch_kv_move(const PlanView&, int32_t, int32_t, bool, const void*, const void*, void*, void*, hipStream_t) {
   return hipErrorNotSupported;
 }
+hipError_t launch_split_planes(const float*, void*, int64_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_silu_bwd(const float*, const void*, const void*, void*, void*, int64_t, hipStream_t) {
+  return hipErrorNotSupported;
+}
 }  // namespace psattn
