@@ -48,7 +48,8 @@ using namespace dev;
 // rows stream through LDS one step at a time (a step is a 32-row subtile of one query head:
 // Q, dO and their LSE log2 e and Delta), in a five-deep ring.  Iteration i issues the dV/dK
 // MFMAs of step i-1 (dV += P^T dO, dK += dS^T Q), then the S and dP MFMAs of step i+1, and
-// between them computes P = exp2(S c - LSE log2 e) and dS = P (dP - Delta) of step i.
+// between them computes P = exp2(S c - LSE log2 e) and dS = P (dP - Delta) of step i (both scaled by powers
+// of two, see kExpP).
 template <int D, bool REM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_kv_bf16_1w_kernel(BwdArgs a) {
   constexpr int RB = D * 2;
@@ -58,6 +59,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int QB = Q_SUB * RB;              // bytes per Q or dO subtile of one head
   constexpr int NI = Q_SUB / RPI;             // copy instructions per subtile and tensor
   constexpr int KS = D / 16, DB = D / 32;
+  // P is held as 2^10 P (exp2 of its exponent + 10) and dP - Delta as 2^-4 (dP - Delta) (V and Delta scaled),
+  // so dS as 2^6 dS: exact powers of two that put the remainder test's thresholds, P = 2^-9 and
+  // |dS| = 2^-5, at 2.0, the values from which on the highest exponent bit is set
+  constexpr float kExpP = 10.f, kScaleDP = 0.0625f, kUnscaleDK = 1.f / 64, kUnscaleDV = 1.f / 1024;
+  constexpr uint32_t kRemBits = 0x40004000u;  // that bit of two packed bf16
   constexpr int SPB = IDX_BLK / Q_SUB;        // subtiles per staged row block
   constexpr int NR = 5;                       // step ring: steps i-1 .. i+NR-2 (copied NR-2 ahead)
   constexpr int CPS = 2 * NI / 4;             // copies every wave issues per step (Q and dO)
@@ -104,11 +110,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       kreg[s] = as_bf(ld16(kp + 32 * s));
-      vreg[s] = as_bf(ld16(vp + 32 * s));
+      u32x4 v = ld16(vp + 32 * s);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = pack2(bf2f(v[k] & 0xffffu) * kScaleDP, __uint_as_float(v[k] & 0xffff0000u) * kScaleDP);
+      vreg[s] = as_bf(v);
     }
   }
   const int kpos = it.kv_pos0 + 32 * wave + l32;
-  f32x16 dk[DB], dv[DB];
+  f32x16 dk[DB], dv[DB];   // dK / scale * 2^6 and dV * 2^10 (the scaled P and dS below)
 #pragma unroll
   for (int nb = 0; nb < DB; ++nb) {
     dk[nb] = f32x16{};
@@ -213,7 +222,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
   // ---- iteration i, NSLOT MFMA slots in NP pairs:
   //   pairs 0 .. NT-1: dV[nb] += P^T dO and dK[nb] += dS^T Q of step i-1 (pair u = DB*t2 + nb)
-  //   (REM) then, on a step where some P > 2^-9 or |dS| > 2^-5: the same products of the
+  //   (REM) then, on a step where some P >= 2^-9 or |dS| >= 2^-5: the same products of the
   //         remainders P - bf16(P) and dS - bf16(dS), from step i-1's fp32 P and dS
   //   pair NT:         S and dP of step i+1 start as -LSE/scale and -Delta (the statistics pair)
   //   then:            S += Q K^T and dP += dO V^T of step i+1 (pair = k-step s)
@@ -226,7 +235,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // walk, ~2^-8/sqrt(3) * sqrt(sum_i P_ij^2 dO_i^2) at most: on a key that many consumers weight
   // heavily (a shared prefix token with attention-sink-like scores) that grows without bound.
   // With P = hi + lo, both bf16, each term is good to ~2^-16.  A step is left single-rounded only
-  // when all its P <= 2^-9 (each term then off by <= 2^-17) and all |dS| <= 2^-5 (<= 2^-13); the
+  // when all its P < 2^-9 (each term then off by <= 2^-17) and all |dS| < 2^-5 (<= 2^-13); the
   // same holds for dS in dK = dS^T Q.  The forward and dQ products sum over keys, whose weights
   // P_i. add up to 1, and need no remainder terms.
   constexpr int NT = 2 * DB;                  // dV/dK slot pairs
@@ -245,7 +254,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // B = (1, 1, 0, 0, ...) or (0, 0, 1, 1, 0, ...) on every key: one 64-bit LDS read per lane
   // instead of 32 values.  B is zero on lanes 32-63 (k = 8..15), where A repeats the row's pairs.
   bf16x8 bs1 = as_bf(hh ? u32x4{0u, 0u, 0u, 0u} : u32x4{0x3F803F80u, 0u, 0u, 0u});
-  bf16x8 bd1 = as_bf(hh ? u32x4{0u, 0u, 0u, 0u} : u32x4{0u, 0x3F803F80u, 0u, 0u});
+  bf16x8 bd1 = as_bf(hh ? u32x4{0u, 0u, 0u, 0u} : u32x4{0u, 0x3D803D80u, 0u, 0u});   // (2^-4: Delta's scale)
   pin_a(bs1);
   pin_a(bd1);
   auto ld_stat = [&](uint32_t slot_off) __attribute__((always_inline)) {
@@ -268,22 +277,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       }
     }
   };
-  // remainder products of one step, if any of its P > 2^-9 or |dS| > 2^-5 (wave-uniform branch):
-  // Pf/Sf its fp32 P and dS, Ph/Sh their packed bf16, Qs/dOs its ring slot.  The maxima are
-  // eight steps each: step k of the P maximum takes elements {0, 1, 2}, then {2k+1, 2k+2}, then
-  // {15}; step k of the |dS| maximum takes {2k, 2k+1}.
-  constexpr float kRemP = 1.0f / 512, kRemS = 1.0f / 32;
-  auto max_p_step = [&](float& mp, const f32x16& Pf, int k) __attribute__((always_inline)) {
-    if (k == 0) mp = max3f(Pf[0], Pf[1], Pf[2]);
-    else if (k < 7) mp = max3f(mp, Pf[2 * k + 1], Pf[2 * k + 2]);
-    else mp = max2f(mp, Pf[15]);
+  // remainder products of one step, if any of its P >= 2^-9 or |dS| >= 2^-5 (wave-uniform branch):
+  // Pf/Sf its fp32 P and dS, Ph/Sh their packed bf16, Qs/dOs its ring slot.  The test is the OR of the 16
+  // packed dwords, two per step k: half the instructions of the maxima of the 32 fp32 values (the step
+  // is bound by instruction issue; c2 2448 -> 2418 us, c4 4042 -> 3970 us).  bf16 rounding can only raise a
+  // value to the threshold, never below it.
+  auto rem_step = [&](uint32_t& any, const bf16x8 (&Ph)[2], const bf16x8 (&Sh)[2], int k) __attribute__((always_inline)) {
+    const u32x4 x = __builtin_bit_cast(u32x4, k < 4 ? Ph[k / 2] : Sh[(k - 4) / 2]);
+    any = any | x[2 * (k % 2)] | x[2 * (k % 2) + 1];
   };
-  auto max_s_step = [&](float& ms, const f32x16& Sf, int k) __attribute__((always_inline)) {
-    ms = max3abs(k == 0 ? 0.f : ms, Sf[2 * k], Sf[2 * k + 1]);
-  };
-  auto rem_apply = [&](float mp, float ms, const f32x16& Pf, const f32x16& Sf, const bf16x8 (&Ph)[2],
+  auto rem_apply = [&](uint32_t any, const f32x16& Pf, const f32x16& Sf, const bf16x8 (&Ph)[2],
                        const bf16x8 (&Sh)[2], uint32_t Qs, uint32_t dOs) __attribute__((always_inline)) {
-    if (__builtin_amdgcn_ballot_w64(mp > kRemP || ms > kRemS) == 0) return;
+    if (__builtin_amdgcn_ballot_w64((any & kRemBits) != 0) == 0) return;
     bf16x8 pl[2], sl[2];
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) {
@@ -302,13 +307,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   };
   auto remainders = [&](const f32x16& Pf, const f32x16& Sf, const bf16x8 (&Ph)[2], const bf16x8 (&Sh)[2], uint32_t Qs,
                         uint32_t dOs) __attribute__((always_inline)) {
-    float mp = 0.f, ms = 0.f;
+    uint32_t any = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      max_p_step(mp, Pf, k);
-      max_s_step(ms, Sf, k);
-    }
-    rem_apply(mp, ms, Pf, Sf, Ph, Sh, Qs, dOs);
+    for (int k = 0; k < 8; ++k) rem_step(any, Ph, Sh, k);
+    rem_apply(any, Pf, Sf, Ph, Sh, Qs, dOs);
   };
   int h3, subc;                               // head of the copy step i+3 and subtile of min(i+3, nsteps-1)
   // row block staging: block stage_blk is staged in the iteration where to_stage reaches 0
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         // (each result pinned to its slot: the branches of the iteration would otherwise let the
         // compiler sink these products to their first use)
         if constexpr (F(v) == q) {
-          float t = Sc[v] * c;
+          float t = fmaf(Sc[v], c, kExpP);
           anchor(t);
           Sc[v] = t;
         }
@@ -379,16 +381,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
       });
     };
-    // the remainder test of step i-1 runs alongside its dV/dK pairs: the maxima of its fp32 P (in
-    // Sn) and dS (in dPn) take one step per MFMA slot, the P maximum after the dV MFMAs and the
-    // |dS| maximum after the dK MFMAs; the ballot and the remainder products follow the last pair
-    float rem_p = 0.f, rem_s = 0.f;
+    // the remainder test of step i-1 runs alongside its dV/dK pairs, after the dV MFMAs; the ballot and the
+    // remainder products follow the last pair
+    uint32_t rem_any = 0;
     auto slot = [&](auto ic) __attribute__((always_inline)) {
       constexpr int si = decltype(ic)::value;
       constexpr int m = si / 2, w = si % 2;
       if constexpr (si == 0) mask_s(Sc, i, sub0);
       if constexpr (REM && si == 2 * NT) {   // before the statistics pair overwrites Sn / dPn
-        rem_apply(rem_p, rem_s, Sn, dPn, Pp, Sp, Qp, dOp);
+        rem_apply(rem_any, Sn, dPn, Pp, Sp, Qp, dOp);
         sched_fence();
       }
       if constexpr (w == 0) load_frag(m + PF);
@@ -405,18 +406,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         else mma_v(dPn, fo[s], vreg[s]);
       }
       chunk(ic);
-      if constexpr (REM && m < NT) {
-        static_for<8 / NT + (8 % NT ? 1 : 0)>([&](auto jc) __attribute__((always_inline)) {
-          constexpr int k = m * 8 / NT + decltype(jc)::value;
-          if constexpr (k < (m + 1) * 8 / NT) {
-            if constexpr (w == 0) {
-              max_p_step(rem_p, Sn, k);
-              anchor(rem_p);
-            } else {
-              max_s_step(rem_s, dPn, k);
-              anchor(rem_s);
-            }
-          }
+      if constexpr (REM && m < NT && w == 0) {
+        static_for<8 / NT>([&](auto jc) __attribute__((always_inline)) {
+          rem_step(rem_any, Pp, Sp, m * (8 / NT) + decltype(jc)::value);
+          anchor(rem_any);
         });
       }
       if constexpr (si == BAR) {
@@ -591,7 +584,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // the first is written back.  (With a slot load, and for a cached node a read, an add and a write
   // per key, the 16 dependent reads of this epilogue took longer than 256 consumer rows: a call of 16
   // sequences of 256 rows after cached 1024-token prefixes took 516 us in this kernel, now 290 us.)
-  const float scale = a.s.scale;
+  const float scale = a.s.scale * kUnscaleDK;
   uint32_t off[16];   // element offset of the key's row (below 2^31: pools are at most 4 GiB of bf16)
   bool ok[16];
 #pragma unroll
@@ -612,7 +605,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
       for (int nb = 0; nb < DB; ++nb) {
         kd[off[v] + 32 * nb] = dk[nb][v] * scale;
-        vd[off[v] + 32 * nb] = dv[nb][v];
+        vd[off[v] + 32 * nb] = dv[nb][v] * kUnscaleDV;
       }
     }
     return;
@@ -630,7 +623,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (ok[v]) dst[off[v] + 32 * nb] = old[nb][v] + acc[nb][v] * f;
   };
   write(kd, dk, scale);
-  write(vd, dv, 1.f);
+  write(vd, dv, kUnscaleDV);
 }
 
 // ============================================================================================

@@ -235,11 +235,6 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-__device__ __forceinline__ float max3abs(float a, float b, float c) {   // max(a, |b|, |c|)
-  float r;
-  asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
 __device__ __forceinline__ float max2f(float a, float b) {
   float r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -258,6 +253,7 @@ __device__ __forceinline__ float pair_max2(float x) {
 
 // Materialize x here: its computation cannot sink past this point.
 __device__ __forceinline__ void anchor(float& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void anchor(uint32_t& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void anchor(f32x16& x) { asm volatile("" : "+v"(x)); }
 // Move x to VGPRs here (from AGPRs, if it lives there).
 __device__ __forceinline__ void pin_v(f32x16& x) { asm volatile("" : "+v"(x)); }
