@@ -1,5 +1,6 @@
 // Backward kernels: Delta = rowsum(dO * O), dK/dV (keys stationary), dQ (queries stationary),
-// fixed-order reductions of split partial results, and zeroing of pool slots holding no token.
+// fixed-order reductions of split partial results.  (The Delta pass also zeroes the gradients of pool slots
+// holding no token.)
 //
 // bf16 dK/dV kernel (gfx950).  One workgroup = one BkvItem: up to 128 keys of one node and one
 // kv head x a chunk of the rows that consume them -- the node's own later rows and every row of
@@ -1044,10 +1045,23 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 // reads one contiguous span of each tensor and writes one run of each statistic; every lane issues
 // all its loads before the first product.  One pass per workgroup measured fastest (against two
 // and four: more workgroups in flight hide more of the load latency than more loads per lane).
+// Workgroups from pre_blocks on write the zero gradients of the pool slots of this call's blocks that hold
+// no token (no other kernel writes those; a launch of their own made a 65 us step 2 us longer).
 constexpr int PRE_PASSES = 1;
 template <bool BF16>
-__global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a) {
+__global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, unsigned pre_blocks) {
   const int D = a.s.d, hq = a.s.hq, ns = a.s.ns;
+  if (blockIdx.x >= pre_blocks) {
+    const int per_slot = a.s.hkv * D / 4;
+    const int64_t n = (int64_t)a.n_pad * per_slot;
+    for (int64_t idx = (int64_t)(blockIdx.x - pre_blocks) * 256 + threadIdx.x; idx < n;
+         idx += (int64_t)(gridDim.x - pre_blocks) * 256) {
+      const size_t o = (size_t)a.plan.pad_slots[idx / per_slot] * a.s.hkv * D + idx % per_slot * 4;
+      *(f32x4*)(a.dK + o) = f32x4{};
+      *(f32x4*)(a.dV + o) = f32x4{};
+    }
+    return;
+  }
   const int lanes = D / 8;
   const int per_pass = 256 / lanes;
   const int64_t npairs = (int64_t)ns * hq;
@@ -1163,25 +1177,15 @@ __global__ __launch_bounds__(256) void bwd_reduce_dq_kernel(BwdArgs a) {
   }
 }
 
-// pool slots that hold no token get zero gradients
-__global__ __launch_bounds__(256) void bwd_zero_pad_kernel(BwdArgs a) {
-  const int per_slot = a.s.hkv * a.s.d / 4;
-  const int64_t n = (int64_t)a.n_pad * per_slot;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int s = (int)(idx / per_slot), r = (int)(idx % per_slot) * 4;
-    const size_t o = (size_t)a.plan.pad_slots[s] * a.s.hkv * a.s.d + r;
-    *(f32x4*)(a.dK + o) = f32x4{};
-    *(f32x4*)(a.dV + o) = f32x4{};
-  }
-}
-
 }  // namespace
 
 hipError_t launch_bwd_pre(const BwdArgs& a, bool bf16, hipStream_t st) {
   const int pairs_per_block = 256 / (a.s.d / 8) * PRE_PASSES;
-  const dim3 grid((unsigned)(((int64_t)a.s.ns * a.s.hq + pairs_per_block - 1) / pairs_per_block));
-  if (bf16) hipLaunchKernelGGL((bwd_pre_kernel<true>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((bwd_pre_kernel<false>), grid, dim3(256), 0, st, a);
+  const unsigned pre = (unsigned)(((int64_t)a.s.ns * a.s.hq + pairs_per_block - 1) / pairs_per_block);
+  const int64_t pad = (int64_t)a.n_pad * a.s.hkv * a.s.d / 4;
+  const dim3 grid(pre + (unsigned)std::min<int64_t>((pad + 255) / 256, 4096));
+  if (bf16) hipLaunchKernelGGL((bwd_pre_kernel<true>), grid, dim3(256), 0, st, a, pre);
+  else hipLaunchKernelGGL((bwd_pre_kernel<false>), grid, dim3(256), 0, st, a, pre);
   return hipGetLastError();
 }
 
@@ -1228,13 +1232,6 @@ hipError_t launch_bwd_reduce_dq(const BwdArgs& a, bool bf16, hipStream_t st) {
   const dim3 grid(a.n_merge, merge_slices(a.n_merge, (int64_t)a.max_merge_rows * a.s.hq * a.s.d / 4, 256));
   if (bf16) hipLaunchKernelGGL(bwd_reduce_dq_kernel<true>, grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(bwd_reduce_dq_kernel<false>, grid, dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_zero_pad(const BwdArgs& a, hipStream_t st) {
-  const int64_t n = (int64_t)a.n_pad * a.s.hkv * a.s.d / 4;
-  const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(bwd_zero_pad_kernel, dim3(blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -987,8 +987,8 @@ struct Profiler {
 };
 Profiler g_prof;
 const char* kKernelNames[] = {"fwd_main", "fwd_merge",     "bwd_pre", "bwd_kv",   "bwd_dq", "bwd_reduce_kv",
-                              "bwd_reduce_dq", "bwd_zero_pad", "rope",    "kv_scatter", "kv_gather", "split_planes", "silu_bwd"};
-constexpr int kNumKernels = 13;
+                              "bwd_reduce_dq", "rope",       "kv_scatter", "kv_gather", "split_planes", "silu_bwd"};
+constexpr int kNumKernels = 12;
 
 hipEvent_t get_event() {
   if (!g_prof.spare.empty()) {
@@ -1174,7 +1174,6 @@ psattn_status psattn_bwd(const psattn_tree* t, const void* Q, const void* K, con
   if (s == PSATTN_OK && a.n_merge) s = timed(6, st, [&] { return launch_bwd_reduce_dq(a, bf16, st); });
   if (s == PSATTN_OK) s = timed(3, st, [&] { return launch_bwd_kv(a, bf16, st); });
   if (s == PSATTN_OK && a.n_reduce) s = timed(5, st, [&] { return launch_bwd_reduce_kv(a, st); });
-  if (s == PSATTN_OK && a.n_pad) s = timed(7, st, [&] { return launch_bwd_zero_pad(a, st); });
   return s;
 }
 
@@ -1190,7 +1189,7 @@ psattn_status psattn_rope(const psattn_tree* t, void* X, psattn_dtype dtype, int
   if (!(theta > 1.f) || !std::isfinite(theta)) return fail(PSATTN_E_INVALID_ARG, "theta must be finite and > 1");
   if (misaligned(X)) return fail(PSATTN_E_ALIGNMENT, "X must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
-  return timed(8, st, [&] {
+  return timed(7, st, [&] {
     return launch_rope(plan_view(t), (int32_t)t->Ns, heads, t->d, theta, inverse != 0, dtype == PSATTN_BF16, X, st);
   });
 }
@@ -1203,7 +1202,7 @@ psattn_status psattn_kv_scatter(const psattn_tree* t, const void* K_rows, const 
     return fail(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
   const int32_t row_bytes = t->hkv * t->d * (t->dtype == PSATTN_BF16 ? 2 : 4);
-  return timed(9, st, [&] { return launch_kv_move(plan_view(t), (int32_t)t->Ns, row_bytes, true, K_rows, V_rows, K, V, st); });
+  return timed(8, st, [&] { return launch_kv_move(plan_view(t), (int32_t)t->Ns, row_bytes, true, K_rows, V_rows, K, V, st); });
 }
 
 psattn_status psattn_kv_gather(const psattn_tree* t, const float* dK, const float* dV, float* dK_rows, float* dV_rows,
@@ -1214,7 +1213,7 @@ psattn_status psattn_kv_gather(const psattn_tree* t, const float* dK, const floa
     return fail(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
   const int32_t row_bytes = t->hkv * t->d * 4;
-  return timed(10, st, [&] {
+  return timed(9, st, [&] {
     return launch_kv_move(plan_view(t), (int32_t)t->Ns, row_bytes, false, dK, dV, dK_rows, dV_rows, st);
   });
 }
@@ -1224,7 +1223,7 @@ psattn_status psattn_split_planes(const float* X, void* planes, int64_t n, void*
   if (n < 1) return fail(PSATTN_E_INVALID_ARG, "n must be >= 1 (got %lld)", (long long)n);
   if (misaligned(X) || misaligned(planes)) return fail(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
-  return timed(11, st, [&] { return launch_split_planes(X, planes, n, st); });
+  return timed(10, st, [&] { return launch_split_planes(X, planes, n, st); });
 }
 
 psattn_status psattn_silu_bwd(const float* dM_planes, const void* A, const void* B, void* dA_planes, void* dB_planes,
@@ -1234,7 +1233,7 @@ psattn_status psattn_silu_bwd(const float* dM_planes, const void* A, const void*
   if (misaligned(dM_planes) || misaligned(A) || misaligned(B) || misaligned(dA_planes) || misaligned(dB_planes))
     return fail(PSATTN_E_ALIGNMENT, "tensor pointers must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
-  return timed(12, st, [&] { return launch_silu_bwd(dM_planes, A, B, dA_planes, dB_planes, n, st); });
+  return timed(11, st, [&] { return launch_silu_bwd(dM_planes, A, B, dA_planes, dB_planes, n, st); });
 }
 
 psattn_status psattn_tree_refcounts(const psattn_tree* t, int32_t* node_refcount) {

@@ -59,7 +59,6 @@ hipError_t launch_bwd_kv(const BwdArgs& a, bool bf16, hipStream_t st);
 hipError_t launch_bwd_dq(const BwdArgs& a, bool bf16, hipStream_t st);
 hipError_t launch_bwd_reduce_kv(const BwdArgs& a, hipStream_t st);
 hipError_t launch_bwd_reduce_dq(const BwdArgs& a, bool bf16, hipStream_t st);
-hipError_t launch_bwd_zero_pad(const BwdArgs& a, hipStream_t st);
 // the fp32 kernels (psattn_f32.hip), called by the launchers above
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t st);
 hipError_t launch_bwd_dq_f32(const BwdArgs& a, hipStream_t st);
