@@ -271,6 +271,12 @@ double makespan(std::vector<double>& cost, double cus) {
   return end * scale;
 }
 
+// The least that makespan can be; it only grows with finer splits, so that a rule that tries them coarse
+// to fine can stop at the first whose even share is no gain.
+double even_share(const std::vector<double>& cost, double cus) {
+  return std::accumulate(cost.begin(), cost.end(), 0.0) / std::max(1e-9, cus);
+}
+
 // Time of one work item, measured on one workgroup with the card otherwise idle (microseconds):
 // start-up and write-back, and per 64-key tile of a forward and a dQ item together, or per step (32
 // consumer rows of one query head) of a dK/dV item.  The fp32 dK/dV step is one of a 32-key part.
@@ -390,6 +396,21 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // per-node path slot list: slots of sequence positions 0 .. off+len-1
   std::vector<int64_t> kvoff(N);
   t->kv_list.clear();
+  std::vector<int64_t> desc_rows(N, 0);   // rows of the (internal) descendants of each node
+  for (int n = N - 1; n >= 0; --n)
+    if (t->parent[n] >= 0) desc_rows[t->parent[n]] += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
+  {
+    // room for every list up front (address space; only what is written is touched): the paths, the packed
+    // siblings' prefixes (two siblings or more each), and the tiles' and consumers' rows
+    int64_t keys = 0, rows = 2 * t->Ns;
+    for (int n = 0; n < N; ++n) {
+      keys += t->off[n] + t->seg_len[n];
+      if (!t->ext[n] && 2 * t->seg_len[n] <= s.bmq) keys += t->off[n] / 2 + t->seg_len[n];
+      rows += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
+    }
+    t->kv_list.reserve((size_t)std::min<int64_t>(keys, INT32_MAX));
+    t->q_list.reserve((size_t)std::min<int64_t>(rows, INT32_MAX));
+  }
   for (int n = 0; n < N; ++n) {
     std::vector<int> path;
     for (int m = n; m >= 0; m = t->parent[m]) path.push_back(m);
@@ -458,9 +479,6 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // the dK/dV work and the coarse rule of its chunks: a chunk holds at most one CU's share of it, so
   // that a tile whose consumers fit in one share runs as one item, with no partial tiles to write
   // and sum
-  std::vector<int64_t> desc_rows(N, 0);   // rows of the (internal) descendants of each node
-  for (int n = N - 1; n >= 0; --n)
-    if (t->parent[n] >= 0) desc_rows[t->parent[n]] += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
   struct KeyTile { int nk; int64_t nq; };
   std::vector<KeyTile> key_tiles;
   int64_t total_b = 0;
@@ -540,7 +558,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       }
       if (c.size() > 65536) break;
       if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(rows0, base_tiles) <= kNoallocBytes) break;
-      const double time = makespan(c, (double)num_cus / n_chunks) + (moved > 0 ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
+      const double extra = (moved > 0 ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
+      if (cap != INT64_MAX && even_share(c, (double)num_cus / n_chunks) + extra >= kSplitGain * best) break;
+      const double time = makespan(c, (double)num_cus / n_chunks) + extra;
       if (cap == INT64_MAX || time < kSplitGain * best) {
         best = time;
         best_cap = cap;
@@ -579,8 +599,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       // launched as one item: the prefix's keys, then the siblings' own (PART_SIBLINGS)
       const int32_t nq = (int32_t)t->q_list.size() - q_pack;
       sib_items.push_back({q_pack, nq, (int32_t)t->kv_list.size(), (int32_t)(pre + nq), 0, 0, PART_SIBLINGS, (int32_t)(pre / KV_TILE)});
-      const std::vector<int32_t> prefix(t->kv_list.begin() + kvoff[n0], t->kv_list.begin() + kvoff[n0] + pre);
-      t->kv_list.insert(t->kv_list.end(), prefix.begin(), prefix.end());
+      const size_t at = t->kv_list.size();
+      t->kv_list.resize(at + (size_t)pre);
+      std::copy_n(t->kv_list.begin() + kvoff[n0], pre, t->kv_list.begin() + (int64_t)at);
       for (int n : pk) t->kv_list.insert(t->kv_list.end(), node_slots[n].begin(), node_slots[n].end());
       if (t->kv_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "key lists exceed 2^31 entries");
       sib_part.push_back(P);
@@ -755,7 +776,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       if (cap != coarse && bwd_bytes(part_rows, ptiles) > kNoallocBytes &&
           bwd_bytes(part_rows, part_tiles_of(coarse)) <= kNoallocBytes)
         break;
-      const double time = makespan(c, (double)num_cus / t->hkv) + (ptiles ? kMergeLaunch : 0.0) + moved / kMergeBytes;
+      const double extra = (ptiles ? kMergeLaunch : 0.0) + moved / kMergeBytes;
+      if (cap != coarse && even_share(c, (double)num_cus / t->hkv) + extra >= kSplitGain * best) break;
+      const double time = makespan(c, (double)num_cus / t->hkv) + extra;
       if (cap == coarse || time < kSplitGain * best) {
         best = time;
         chunk_rows = cap;
