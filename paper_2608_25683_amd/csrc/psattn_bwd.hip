@@ -968,13 +968,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 #pragma unroll
       for (int mb = 0; mb < DB; ++mb) pin_a(dq[rh][mb]);
   }
+  // rows that this pass leaves to the row-by-row one (packed siblings with results that are not finite)
+  uint32_t redo[NH];
+#pragma unroll
+  for (int rh = 0; rh < NH; ++rh) {
+    redo[rh] = 0;
+    if (SIB && it.part == PART_SIBLINGS) {
+      float z = 0.f;
+#pragma unroll
+      for (int mb = 0; mb < DB; ++mb) z = add_if_finite(dq[rh][mb], z);
+      const uint64_t b = __ballot(row_ok[rh] && !(z == 0.f));
+      redo[rh] = (uint32_t)b | (uint32_t)(b >> 32);
+    }
+  }
   // the exact Delta' = Delta + (row sum of dS'), as the (hi, lo) bf16 start value -Delta' of the
   // dK/dV kernel's dP accumulators; a row whose key range was split leaves its part of the sum to
   // the fixed-order reduction of the pieces
 #pragma unroll
   for (int rh = 0; rh < NH; ++rh) {
     const float e = pair_sum(eps[rh]);   // lanes l and l ^ 32 hold different keys of one row
-    if (hh == 0 && row_ok[rh]) {
+    if (hh == 0 && row_ok[rh] && !(redo[rh] >> l32 & 1)) {
       if (it.part < 0) {
         const uint32_t w = split_bf16(-del[rh]);
         const float d0 = bf2f(w & 0xffffu) + bf2f(w >> 16);   // the -Delta the dP products started from
@@ -993,10 +1006,28 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   constexpr int QS = D * 4 + 16;
   constexpr int CPRQ = D * 4 / 16, RPIQ = 64 / CPRQ;   // 16-byte chunks per row, rows per instruction
   const float scale = a.s.scale;
+  auto redo_rows = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int rh = 0; rh < NH; ++rh)
+#pragma unroll 1
+      for (uint32_t todo = redo[rh]; todo; todo &= todo - 1) {
+        const int l = __builtin_ctz(todo);
+        const RowPath path(kvl, it, __builtin_amdgcn_readlane(lim[rh], l), __builtin_amdgcn_readlane((int)gap[rh], l));
+        const size_t pair = (size_t)__builtin_amdgcn_readlane(row[rh], l) * a.s.hq + head[rh];
+        const uint32_t w = split_bf16(-lane_value(del[rh], l));
+        const float d0 = bf2f(w & 0xffffu) + bf2f(w >> 16);   // as above
+        float x[D / 64];
+        const float e = row_dq<D, true>(x, path, (const bf16_t*)a.Q + pair * D, (const bf16_t*)a.dO + pair * D, Kb, Vb,
+                                        (size_t)a.s.hkv * D, a.s.scale, lane_value(lse2[rh], l) / kLog2e, d0, lane);
+        if (lane == 0) ((uint32_t*)a.kv_nd)[pair] = split_bf16(d0 - e);
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) a.dQ[pair * D + (D / 64) * lane + i] = x[i] * a.s.scale;
+      }
+  };
   if constexpr (NW * 32 * QS > NS * 2 * TB) {
 #pragma unroll
     for (int rh = 0; rh < NH; ++rh) {
-      if (!row_ok[rh]) continue;
+      if (!row_ok[rh] || (redo[rh] >> l32 & 1)) continue;
       float* dst = it.part < 0 ? a.dQ + ((size_t)row[rh] * a.s.hq + head[rh]) * D
                                : a.part_dq + (((size_t)it.part + ridx[rh]) * a.s.hq + head[rh]) * D;
 #pragma unroll
@@ -1007,6 +1038,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
               f32x4{dq[rh][mb][4 * g4] * scale, dq[rh][mb][4 * g4 + 1] * scale, dq[rh][mb][4 * g4 + 2] * scale,
                     dq[rh][mb][4 * g4 + 3] * scale};
     }
+    if constexpr (SIB) redo_rows();
     return;
   }
   uint8_t* qt = &smem[0][0][0] + wave * 32 * QS;
@@ -1030,11 +1062,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
       const int rl = k * RPIQ + lane / CPRQ;
       const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)dsto, rl);
       const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(dsto >> 32), rl);
-      const int ok = __shfl((int)row_ok[rh], rl);
+      const int ok = __shfl((int)(row_ok[rh] && !(redo[rh] >> l32 & 1)), rl);
       const u32x4 v = *(const u32x4*)(qt + rl * QS + 16 * ch);
       if (ok) *(u32x4*)(base + (((size_t)hi << 32) | lo) + 4 * ch) = v;
     }
   }
+  if constexpr (SIB) redo_rows();
 }
 
 // ============================================================================================

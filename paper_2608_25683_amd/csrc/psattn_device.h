@@ -318,5 +318,103 @@ __device__ __forceinline__ RowKeys row_keys(const FwdItem& it, int nkv, int ridx
   return {pre + ridx, (uint32_t)(ridx - (qpos - pre))};
 }
 
+// ---- Packed siblings and values that are not finite.  A hidden key has probability 0, but the products
+// take its K and V all the same, and 0 x inf and 0 x NaN are NaN: an infinity or a NaN in one sibling's own
+// keys reaches the rows of every sibling in its item (their maxima and sums, hidden scores being -inf,
+// stay right).  The kernels with such items therefore test their accumulators and compute a row that is not finite
+// again by itself, from the keys that it sees and no others.  One wavefront per row, with the keys on its lanes
+// for the scores and head_dim on its lanes for the sums, in fp32: slow (tens of microseconds per row of 4096 keys), and
+// only ever run for such values.
+struct RowPath {   // the keys that one row sees: entries 0 .. pre - 1 of kvl, then those from pre + gap on, n in all
+  const int* kvl;
+  int pre, gap, n;
+  __device__ __forceinline__ RowPath(const int* kvl_, const FwdItem& it, int lim, int gap_)
+      : kvl(kvl_), pre(it.nkv - it.nq), gap(gap_), n(lim + 1 - gap_) {}
+  __device__ __forceinline__ int slot(int j) const {
+    j = min(j, n - 1);
+    return kvl[j < pre ? j : j + gap];
+  }
+};
+// adds 0 if every element of x is finite, else NaN
+template <class V>
+__device__ __forceinline__ float add_if_finite(const V& x, float z) {
+#pragma unroll
+  for (int e = 0; e < (int)(sizeof(V) / 4); ++e) z = fmaf(x[e], 0.f, z);
+  return z;
+}
+// element i of a bf16 or fp32 row
+template <bool BF16>
+__device__ __forceinline__ float elem(const void* p, int i) {
+  if (BF16) return bf2f(((const bf16_t*)p)[i]);
+  return ((const float*)p)[i];
+}
+template <bool BF16>
+__device__ __forceinline__ const void* elem_ptr(const void* p, size_t i) {
+  return (const uint8_t*)p + i * (BF16 ? 2 : 4);
+}
+template <int D, bool BF16>
+__device__ __forceinline__ float row_dot(const void* x, const void* y) {
+  float s = 0.f;
+#pragma unroll 1
+  for (int i = 0; i < D; i += 8)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s = fmaf(elem<BF16>(x, i + e), elem<BF16>(y, i + e), s);
+  return s;
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
+}
+// acc[e] += sum_i w(lane i) * X[row(lane i)][E lane + e] over the first n lanes (E = D / 64)
+template <int D, bool BF16>
+__device__ __forceinline__ void add_rows(float (&acc)[D / 64], const void* X, size_t stride, int row, float w, int n, int lane) {
+  constexpr int E = D / 64;
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    const float wi = lane_value(w, i);
+    const void* x = elem_ptr<BF16>(X, (size_t)__builtin_amdgcn_readlane(row, i) * stride + E * lane);
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = fmaf(wi, elem<BF16>(x, e), acc[e]);
+  }
+}
+// exp(scale s - ref), as the kernels of the type form it
+template <bool BF16>
+__device__ __forceinline__ float row_exp(float s, float scale, float ref) {
+  if (BF16) return fast_exp2(fmaf(s, scale * kLog2e, -ref * kLog2e));
+  return expf(s * scale - ref);
+}
+// O of one row: sum_j exp(scale q.k_j - m) inv v_j; lane l returns elements E l + e
+template <int D, bool BF16>
+__device__ __forceinline__ void row_fwd(float (&o)[D / 64], const RowPath& path, const void* q, const void* K, const void* V,
+                                        size_t stride, float scale, float m, float inv, int lane) {
+#pragma unroll
+  for (int e = 0; e < D / 64; ++e) o[e] = 0.f;
+#pragma unroll 1
+  for (int j0 = 0; j0 < path.n; j0 += 64) {
+    const int slot = path.slot(j0 + lane);
+    const float s = row_dot<D, BF16>(q, elem_ptr<BF16>(K, (size_t)slot * stride));
+    const float p = row_exp<BF16>(s, scale, m) * inv;
+    add_rows<D, BF16>(o, V, stride, slot, p, min(64, path.n - j0), lane);
+  }
+}
+// dQ / scale of one row: sum_j ds_j k_j with ds_j = exp(scale q.k_j - lse) (dO.v_j + nd); returns sum_j ds_j
+template <int D, bool BF16>
+__device__ __forceinline__ float row_dq(float (&dq)[D / 64], const RowPath& path, const void* q, const void* dO, const void* K,
+                                        const void* V, size_t stride, float scale, float lse, float nd, int lane) {
+  float sum = 0.f;
+#pragma unroll
+  for (int e = 0; e < D / 64; ++e) dq[e] = 0.f;
+#pragma unroll 1
+  for (int j0 = 0; j0 < path.n; j0 += 64) {
+    const int slot = path.slot(j0 + lane), n = min(64, path.n - j0);
+    const float s = row_dot<D, BF16>(q, elem_ptr<BF16>(K, (size_t)slot * stride));
+    const float dp = row_dot<D, BF16>(dO, elem_ptr<BF16>(V, (size_t)slot * stride)) + nd;
+    const float ds = lane < n ? row_exp<BF16>(s, scale, lse) * dp : 0.f;
+    sum += ds;
+    add_rows<D, BF16>(dq, K, stride, slot, ds, n, lane);
+  }
+  for (int w = 32; w >= 1; w >>= 1) sum += __shfl_xor(sum, w);
+  return sum;
+}
+
 }  // namespace dev
 }  // namespace psattn

@@ -93,6 +93,17 @@ __device__ __forceinline__ void put_tile(float* tile, const f32x16 (&acc)[D / 32
   }
 }
 
+// Lanes whose row (eight lanes each) holds a value that is not finite, in an item of packed siblings
+template <bool SIB>
+__device__ __forceinline__ uint64_t redo_lanes(const FwdItem& it, bool bad) {
+  if (!SIB || it.part != PART_SIBLINGS) return 0;
+  uint64_t b = __ballot(bad);
+  b |= b >> 4;
+  b |= b >> 2;
+  b |= b >> 1;
+  return (b & 0x0101010101010101ull) * 0xff;
+}
+
 // ============================================================================================
 // Forward: one FwdItem of up to 32 rows x one head; wave w takes the 32-key blocks w, w + 4, ...
 template <int D, bool SIB>
@@ -163,8 +174,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128
   }
   __syncthreads();
   // eight threads per row: the waves' results against the common maximum, in wave order
-  const int r = tid >> 3;
-  if (r >= it.nq) return;
+  const int r = min(tid >> 3, it.nq - 1);
   float m = kNegInf, l = 0.f, w[NW];
 #pragma unroll
   for (int i = 0; i < NW; ++i) m = fmaxf(m, s_m[i][r]);
@@ -176,22 +186,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128
   const float inv = l > 0.f ? 1.f / l : 0.f;
   const float lse = l > 0.f ? m + logf(l) : kNegInf;
   const int orow = a.plan.q_list[it.q_off + r];
+  const bool row_ok = tid >> 3 < it.nq;
   float* op;
   if (it.part < 0) {
     op = (float*)a.O + ((size_t)orow * a.s.hq + head) * D;
-    if ((tid & 7) == 0) a.LSE[(size_t)head * a.s.ns + orow] = lse;
+    if (row_ok && (tid & 7) == 0) a.LSE[(size_t)head * a.s.ns + orow] = lse;
   } else {
     const size_t prow = (size_t)it.part + r;
     op = a.part_o + (prow * a.s.hq + head) * D;
-    if ((tid & 7) == 0) a.part_lse[prow * a.s.hq + head] = lse;
+    if (row_ok && (tid & 7) == 0) a.part_lse[prow * a.s.hq + head] = lse;
   }
+  f32x4 x[D / 32];
+  float z = 0.f;
 #pragma unroll
   for (int c = 0; c < D / 32; ++c) {
-    const int d = 4 * ((tid & 7) + 8 * c);
-    f32x4 x = f32x4{};
+    x[c] = f32x4{};
 #pragma unroll
-    for (int i = 0; i < NW; ++i) x += w[i] * *(const f32x4*)&s_o[i][r * LS + d];
-    *(f32x4*)(op + d) = x * inv;
+    for (int i = 0; i < NW; ++i) x[c] += w[i] * *(const f32x4*)&s_o[i][r * LS + 4 * ((tid & 7) + 8 * c)];
+    x[c] *= inv;
+    z = add_if_finite(x[c], z);
+  }
+  const uint64_t redo = redo_lanes<SIB>(it, row_ok && !(z == 0.f));
+  if (row_ok && !(redo >> lane & 1)) {
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c) *(f32x4*)(op + 4 * ((tid & 7) + 8 * c)) = x[c];
+  }
+  if constexpr (SIB) {
+    for (uint64_t todo = redo & 0x0101010101010101ull; todo; todo &= todo - 1) {   // the row's first thread
+      const int l = __builtin_ctzll(todo), i = 8 * wave + l / 8;
+      const int qpos = a.plan.q_pos[it.q_off + i];
+      const RowKeys keys = row_keys<SIB>(it, it.nkv, i, qpos);
+      const size_t at = ((size_t)__builtin_amdgcn_readlane(orow, l) * a.s.hq + head) * D;
+      float y[D / 64];
+      row_fwd<D, false>(y, RowPath(kvl, it, keys.lim, (int)keys.gap), (const float*)a.Q + at, Kh, Vh, kv_stride,
+                        a.s.scale, lane_value(m, l), lane_value(inv, l), lane);
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) ((float*)a.O)[at + (D / 64) * lane + e] = y[e];
+    }
   }
 }
 
@@ -251,17 +282,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   put_tile<D>(s_q[wave], dq, l32, hh);
   __syncthreads();
-  const int r = tid >> 3;
-  if (r >= it.nq) return;
+  const int r = min(tid >> 3, it.nq - 1);
+  const bool row_ok = tid >> 3 < it.nq;
   float* dst = it.part < 0 ? a.dQ + ((size_t)a.plan.q_list[it.q_off + r] * a.s.hq + head) * D
                            : a.part_dq + (((size_t)it.part + r) * a.s.hq + head) * D;
+  f32x4 x[D / 32];
+  float z = 0.f;
 #pragma unroll
   for (int c = 0; c < D / 32; ++c) {
-    const int d = 4 * ((tid & 7) + 8 * c);
-    f32x4 x = f32x4{};
+    x[c] = f32x4{};
 #pragma unroll
-    for (int i = 0; i < NW; ++i) x += *(const f32x4*)&s_q[i][r * LS + d];
-    *(f32x4*)(dst + d) = x * a.s.scale;
+    for (int i = 0; i < NW; ++i) x[c] += *(const f32x4*)&s_q[i][r * LS + 4 * ((tid & 7) + 8 * c)];
+    x[c] *= a.s.scale;
+    z = add_if_finite(x[c], z);
+  }
+  const uint64_t redo = redo_lanes<SIB>(it, row_ok && !(z == 0.f));
+  if (row_ok && !(redo >> lane & 1)) {
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c) *(f32x4*)(dst + 4 * ((tid & 7) + 8 * c)) = x[c];
+  }
+  if constexpr (SIB) {
+    for (uint64_t todo = redo & 0x0101010101010101ull; todo; todo &= todo - 1) {   // the row's first thread
+      const int i = 8 * wave + __builtin_ctzll(todo) / 8;
+      const int qrow = a.plan.q_list[it.q_off + i], qpos = a.plan.q_pos[it.q_off + i];
+      const RowKeys keys = row_keys<SIB>(it, it.nkv, i, qpos);
+      const size_t at = ((size_t)qrow * a.s.hq + head) * D;
+      float y[D / 64];
+      row_dq<D, false>(y, RowPath(kvl, it, keys.lim, (int)keys.gap), (const float*)a.Q + at, (const float*)a.dO + at, Kh, Vh,
+                       kv_stride, a.s.scale, a.LSE[(size_t)head * a.s.ns + qrow],
+                       -a.delta[(size_t)qrow * a.s.hq + head], lane);
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) a.dQ[at + (D / 64) * lane + e] = y[e] * a.s.scale;
+    }
   }
 }
 

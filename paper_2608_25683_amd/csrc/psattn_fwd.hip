@@ -417,6 +417,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 #pragma unroll
       for (int mb = 0; mb < DB; ++mb) pin_a(oacc[rh][mb]);
   }
+  // rows that this pass leaves to the row-by-row one (packed siblings with results that are not finite)
+  uint32_t redo[NH];
+#pragma unroll
+  for (int rh = 0; rh < NH; ++rh) {
+    redo[rh] = 0;
+    if (SIB && it.part == PART_SIBLINGS) {
+      float z = 0.f;
+#pragma unroll
+      for (int mb = 0; mb < DB; ++mb) z = add_if_finite(oacc[rh][mb], z);
+      const uint64_t b = __ballot(row_ok[rh] && !(z == 0.f));
+      redo[rh] = (uint32_t)b | (uint32_t)(b >> 32);
+    }
+  }
 
   // Unsplit items write O as whole rows: each wave stages its normalized bf16 rows in the LDS ring
   // (free once every wave has finished the PV products above; padded row stride OS), then copies
@@ -480,7 +493,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
         const int rl = k * RPIO + lane / CPRO;          // staged row; its half is (k * RPIO) / 32
         const int rh = (k * RPIO) / 32;
         const int r = __shfl(row[rh], rl % 32);
-        const int ok = __shfl((int)row_ok[rh], rl % 32);
+        const int ok = __shfl((int)(row_ok[rh] && !(redo[rh] >> l32 & 1)), rl % 32);
         const u32x4 v = *(const u32x4*)(ot + rl * OS + 16 * ch);
         if (ok) *(u32x4*)(dst + ((size_t)r * a.s.hq + head[rh]) * RB + 16 * ch) = v;
       }
@@ -489,6 +502,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
     write_rows(false, (uint8_t*)a.O);
     // (the staging area is the wave's own: its LDS reads above complete before the writes below)
     if (a.O_lo) write_rows(true, (uint8_t*)a.O_lo);
+  }
+  if constexpr (SIB) {
+#pragma unroll
+    for (int rh = 0; rh < NH; ++rh)
+#pragma unroll 1
+      for (uint32_t todo = redo[rh]; todo; todo &= todo - 1) {
+        const int l = __builtin_ctz(todo);
+        const RowPath path(kvl, it, __builtin_amdgcn_readlane(lim[rh], l), __builtin_amdgcn_readlane((int)gap[rh], l));
+        const size_t at = ((size_t)__builtin_amdgcn_readlane(row[rh], l) * a.s.hq + head[rh]) * D;
+        float o[D / 64];
+        row_fwd<D, true>(o, path, (const bf16_t*)a.Q + at, Kb, Vb, (size_t)a.s.hkv * D, a.s.scale,
+                         lane_value(m_run[rh], l) * a.s.scale, lane_value(inv[rh], l), lane);
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) {
+          const uint32_t w = split_bf16(o[e]);
+          const size_t i = at + (D / 64) * lane + e;
+          ((bf16_t*)a.O)[i] = (bf16_t)w;
+          if (a.O_lo) ((bf16_t*)a.O_lo)[i] = (bf16_t)(w >> 16);
+        }
+      }
   }
 }
 

@@ -1,0 +1,66 @@
+"""Packed siblings stay independent samples: an infinity or a NaN in one sibling's own K or V, or one
+whose dO . V overflows fp32, leaves the rows of the others in its tile, and the gradients of their own keys,
+what they are without it.  Several tiles per pack, siblings across 32-row subtiles, single rows, group sizes
+that do and do not divide 8, both head dims and types; against the fp64 oracle of the finite inputs."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2608_25683_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+import parity_helpers as H  # noqa: E402
+
+SEG = {"bf16": [130, 16, 9, 30, 1, 16, 32, 7, 16], "fp32": [130, 16, 9, 5, 1, 16, 7, 2, 14]}
+
+
+def _spoil(kind, K, V, slots):
+    """One value of the node's last token (every kv head), so that all but its last row see finite keys."""
+    s = int(slots[-1])
+    if kind == "inf_v":
+        V[s, :, 3] = float("inf")
+    elif kind == "nan_k":
+        K[s, :, 5] = float("nan")
+    elif kind == "nan_v":
+        V[s, :, 0] = float("nan")
+    else:   # finite: the other rows' dO . V overflows
+        V[s] = 3e38
+
+
+@pytest.mark.parametrize("kind", ["inf_v", "nan_v", "nan_k", "huge_v"])
+@pytest.mark.parametrize("dtype,hq,hkv,d", [("bf16", 8, 2, 128), ("bf16", 5, 1, 64), ("bf16", 2, 2, 64), ("bf16", 7, 1, 128),
+                                            ("fp32", 4, 2, 128), ("fp32", 3, 1, 64)])
+def test_siblings_do_not_see_each_other(dtype, hq, hkv, d, kind):
+    from paper_2608_25683_amd import psattn as P
+    seg = SEG[dtype]
+    wl = W.custom([-1] + [0] * (len(seg) - 1), seg, list(range(1, len(seg))), hq=hq, hkv=hkv, d=d, dtype=dtype, seed=81,
+                  block_policy=lambda n: W.blocks_fixed(n, 16))
+    t = wl.tree
+    tree = P.Tree.from_workload(wl, device="cuda")
+    assert (tree.plan_array("fwd_launch")[:, 6] == -2).any()
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to("cuda").to(dt)
+    Q, K, V, dO = up(wl.Q), up(wl.K_pool), up(wl.V_pool), up(wl.dO)
+    slots = t.row_slots()
+    rows = [np.arange(int(o), int(o) + int(n)) for o, n in zip(t.row_off, t.seg_len)]
+    bad = 3
+    _spoil(kind, K, V, slots[rows[bad]])
+    print(f"siblings {dtype} {hq}/{hkv} d={d} {kind}", file=sys.stderr, flush=True)
+    O_lo = torch.empty_like(Q) if dtype == "bf16" else None
+    O, LSE = P.psattn_fwd(tree, Q, K, V, O_lo=O_lo)
+    dQ, dK, dV = P.psattn_bwd(tree, Q, K, V, O, LSE, dO, O_lo=O_lo)
+    torch.cuda.synchronize()
+    Or, LSEr, dQr, dKr, dVr = H.run_oracle(wl)
+    num = lambda x: x.double().cpu().numpy()
+    keep = np.concatenate([r for n, r in enumerate(rows) if n not in (0, bad)])
+    own = slots[keep]
+    for name, got, ref in (("O", num(O)[keep], Or[keep]), ("LSE", num(LSE)[:, keep], LSEr[:, keep]),
+                           ("dQ", num(dQ)[keep], dQr[keep]), ("dK", num(dK)[own], dKr[own]), ("dV", num(dV)[own], dVr[own]),
+                           ("root O", num(O)[rows[0]], Or[rows[0]]), ("root dQ", num(dQ)[rows[0]], dQr[rows[0]])):
+        H.compare(name, got, ref, dtype)
+    # the spoilt sibling itself: its last row sees the value (huge_v: a finite one)
+    last = num(O)[rows[bad][-1]]
+    assert np.isfinite(last).all() == (kind == "huge_v")
