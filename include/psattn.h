@@ -125,7 +125,8 @@ typedef struct {
   int64_t num_rows;         /* Ns */
   int64_t unshared_tokens;  /* Nu = sum over samples of path length */
   int64_t visible_pairs;    /* sum over rows of visible keys (per query head) */
-  int64_t fwd_items, fwd_merges, bkv_items, bkv_reduces, pad_slots;
+  int64_t fwd_items, fwd_merges;   /* as launched */
+  int64_t bkv_items, bkv_reduces, pad_slots;
   int64_t fwd_partial_rows, bkv_partial_tiles;
   int64_t plan_bytes;       /* == psattn_tree_device_bytes */
   int32_t q_tile_rows, kv_tile_keys, bkv_tile_keys, head_chunk;
@@ -335,8 +336,10 @@ psattn_status psattn_tree_get_info(const psattn_tree* tree, psattn_tree_info* in
  *   0 row_pos [Ns]            sequence position of each packed row
  *   1 q_list                  packed row indices referenced by work items
  *   2 kv_list                 pool slots referenced by work items
- *   3 fwd_items [n][8]        q_off nq kv_off nkv kv_pos0 head0 part nfull
- *   4 fwd_merges [n][4]       q_off nq part0 nparts
+ *   3 fwd_items [n][8]        q_off nq kv_off nkv kv_pos0 head0 part nfull, as independent pieces: where packed
+ *                             siblings are launched as one item (10), its prefix and every sibling's own
+ *                             keys apart, with partial rows from fwd_partial_rows on that only these pieces have
+ *   4 fwd_merges [n][4]       q_off nq part0 nparts, of those pieces
  *   5 bkv_items [n][10]       kv_off nk kv_pos0 q_off nq hk part mask_lo mask_hi acc
  *   6 bkv_reduces [n][8]      kv_off nk hk part0 nparts acc 0 0
  *   7 pad_slots [n]           pool slots that hold no token

@@ -62,11 +62,12 @@ struct psattn_tree {
   // plan (host copy)
   Shape shape{};
   std::vector<int32_t> row_pos, row_slot, q_list, q_pos, kv_list, pad_slots;
-  std::vector<FwdItem> fwd;
+  std::vector<FwdItem> fwd;         // as independent pieces (inspection; see build_plan)
   std::vector<MergeEntry> merge;
   std::vector<BkvItem> bkv;
   std::vector<ReduceEntry> reduce;
   int64_t fwd_part_rows = 0, bkv_part_tiles = 0;
+  int64_t piece_part_rows = 0;      // partial rows that only the independent pieces have, behind fwd_part_rows
   int32_t max_merge_rows = 0, siblings = 0;
   // the forward / dQ items and merge records of the device image (see build_plan)
   std::vector<FwdItem> fwd_launch;
@@ -322,7 +323,7 @@ psattn_status check_plan(const psattn_tree* t) {
     if (f.nq < 1 || f.nq > s.bmq || f.q_off < 0 || (int64_t)f.q_off + f.nq > nql) return bad("forward item rows", (int64_t)i);
     if (f.nkv < 1 || f.kv_off < 0 || (int64_t)f.kv_off + f.nkv > nkl) return bad("forward item keys", (int64_t)i);
     if (f.head0 < 0 || f.head0 + s.hc > s.hq || f.head0 / s.g != (f.head0 + s.hc - 1) / s.g) return bad("forward item heads", (int64_t)i);
-    if (f.part < -1 || (f.part >= 0 && (int64_t)f.part + f.nq > t->fwd_part_rows)) return bad("forward item partial rows", (int64_t)i);
+    if (f.part < -1 || (f.part >= 0 && (int64_t)f.part + f.nq > t->fwd_part_rows + t->piece_part_rows)) return bad("forward item partial rows", (int64_t)i);
     if (f.nfull < 0 || (int64_t)f.nfull * KV_TILE > f.nkv + KV_TILE - 1) return bad("forward item unmasked tiles", (int64_t)i);
   }
   for (size_t i = 0; i < t->fwd_launch.size(); ++i) {
@@ -333,12 +334,16 @@ psattn_status check_plan(const psattn_tree* t) {
     if (f.part < PART_SIBLINGS || (f.part >= 0 && (int64_t)f.part + f.nq > t->fwd_part_rows)) return bad("launched item partial rows", (int64_t)i);
     if (f.part == PART_SIBLINGS && f.nkv < f.nq) return bad("launched sibling keys", (int64_t)i);
   }
-  for (size_t i = 0; i < t->merge.size(); ++i) {
-    const MergeEntry& m = t->merge[i];
+  auto check_merge = [&](const MergeEntry& m, int64_t rows, size_t i) {
     if (m.nq < 1 || m.q_off < 0 || (int64_t)m.q_off + m.nq > nql) return bad("merge rows", (int64_t)i);
-    if (m.nparts < 1 || m.part0 < 0 || (int64_t)m.part0 + (int64_t)(m.nparts - 1) * s.bmq + m.nq > t->fwd_part_rows)
+    if (m.nparts < 1 || m.part0 < 0 || (int64_t)m.part0 + (int64_t)(m.nparts - 1) * s.bmq + m.nq > rows)
       return bad("merge partial rows", (int64_t)i);
-  }
+    return PSATTN_OK;
+  };
+  for (size_t i = 0; i < t->merge.size(); ++i)
+    if (check_merge(t->merge[i], t->fwd_part_rows + t->piece_part_rows, i) != PSATTN_OK) return PSATTN_E_INTERNAL;
+  for (size_t i = 0; i < t->merge_launch.size(); ++i)
+    if (check_merge(t->merge_launch[i], t->fwd_part_rows, i) != PSATTN_OK) return PSATTN_E_INTERNAL;
   for (size_t i = 0; i < t->bkv.size(); ++i) {
     const BkvItem& b = t->bkv[i];
     if (b.nk < 1 || b.nk > BKV_TILE || b.kv_off < 0 || (int64_t)b.kv_off + b.nk > nkl) return bad("dK/dV item keys", (int64_t)i);
@@ -421,11 +426,11 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   }
 
   // ---------------- forward / dQ tasks: query tile x key range (pieces) ----------------
-  struct FTask { int32_t q_off, nq, kv_off, kv_pos0, nkv, min_qpos, part; double cost; };
+  struct FTask { int32_t q_off, nq, kv_off, kv_pos0, nkv, min_qpos, part; double cost; bool launched = true; };
   std::vector<FTask> ftasks;
-  std::vector<MergeEntry> merges;
+  std::vector<MergeEntry> merges, piece_merges;   // launched; of unsplit packs' pieces
   t->q_list.clear();
-  int64_t part_rows = 0;
+  int64_t part_rows = 0, piece_rows = 0;
   // Sibling packing: children of one parent whose segments fill at most half a query tile share
   // the key range [0, off) of their common prefix.  Their rows are packed (first fit, child
   // order) into one tile for that range, and each node keeps an item of its own keys
@@ -434,7 +439,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // (part0 = P + o, npref + 1 parts) combines them.  (An unsplit prefix, npref = 1, is launched with the
   // siblings' own keys behind it as one item that writes its results directly: no partial rows, and no
   // item start-up per sibling for its few own keys.  256 branches of 16 rows on a 4096-token prompt, 32/8
-  // heads: forward + merge 507 -> 388 us, dQ + sum 636 -> 518 us.)
+  // heads: forward + merge 507 -> 388 us, dQ + sum 636 -> 518 us.  Its pieces are kept for inspection only, with
+  // partial rows numbered behind those of the workspace.)
   std::vector<char> packed(N, 0);
   std::vector<std::vector<int>> packs;
   for (int p = 0; p < N; ++p) {
@@ -514,12 +520,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     // merge passes; a long range on an idle chip costs more (a 4096-token cached prefix and 48 new
     // rows: 218 us whole).
     std::vector<std::pair<int64_t, int>> ranges;   // (keys, rows) of every splittable range
-    int64_t rows0 = 0;                             // partial rows there are in any case
     std::vector<int> pack_rows(packs.size(), 0);
-    for (size_t i = 0; i < packs.size(); ++i) {
+    for (size_t i = 0; i < packs.size(); ++i)
       for (int n : packs[i]) pack_rows[i] += t->seg_len[n];
-      rows0 += 2 * s.bmq;
-    }
     for (int n = 0; n < N; ++n)
       for (int a0 = 0; !packed[n] && !t->ext[n] && a0 < t->seg_len[n]; a0 += s.bmq) {
         const int a1 = std::min<int>(t->seg_len[n], a0 + s.bmq);
@@ -532,7 +535,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       cap_tiles = cap;
       std::vector<double> c;
       double moved = 0.0;
-      int64_t prows = rows0;
+      int64_t prows = 0;
       for (size_t i = 0; i < packs.size(); ++i) {
         const int64_t pre = t->off[packs[i][0]], k = piece_keys(pre);
         const int n = num_pieces(pre);
@@ -544,7 +547,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
           c.push_back(ic.fwd0 + ic.fwd_tile * (double)((std::min(k, pre - j * k) + KV_TILE - 1) / KV_TILE));
         for (int m : packs[i]) c.push_back(ic.fwd0 + ic.fwd_tile * (double)((t->seg_len[m] + KV_TILE - 1) / KV_TILE));
         moved += 4.0 * (n + 1) * pack_rows[i] * t->hq * t->d * 4.0;
-        prows += (int64_t)(n - 1) * s.bmq;
+        prows += (int64_t)(n + 1) * s.bmq;
       }
       for (const auto& r : ranges) {
         const int n = num_pieces(r.first);
@@ -557,7 +560,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
         }
       }
       if (c.size() > 65536) break;
-      if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(rows0, base_tiles) <= kNoallocBytes) break;
+      if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(0, base_tiles) <= kNoallocBytes) break;
       const double extra = (moved > 0 ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
       if (cap != INT64_MAX && even_share(c, (double)num_cus / n_chunks) + extra >= kSplitGain * best) break;
       const double time = makespan(c, (double)num_cus / n_chunks) + extra;
@@ -569,14 +572,15 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     cap_tiles = best_cap;
   }
   std::vector<FwdItem> sib_items;   // the launched items of unsplit packs (head0 per chunk)
-  std::vector<int32_t> sib_part;    // and the first partial row of the items and merges they replace
   for (const std::vector<int>& pk : packs) {
     const int n0 = pk[0];
     const int64_t pre = t->off[n0];   // the common prefix: every sibling starts at the same position
     const int npref = num_pieces(pre);
     const int64_t split_keys = piece_keys(pre);
-    const int32_t P = (int32_t)part_rows;
-    part_rows += (int64_t)(npref + 1) * s.bmq;
+    const bool whole = npref == 1;
+    int64_t& rows_used = whole ? piece_rows : part_rows;
+    const int32_t P = (int32_t)rows_used;
+    rows_used += (int64_t)(npref + 1) * s.bmq;
     const int32_t q_pack = (int32_t)t->q_list.size();
     int rows = 0;
     for (int n : pk)
@@ -593,9 +597,10 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       f.min_qpos = (int32_t)pre;
       f.part = P + j * s.bmq;
       f.cost = (double)f.nq * (double)f.nkv + 4096.0;
+      f.launched = !whole;
       ftasks.push_back(f);
     }
-    if (npref == 1) {
+    if (whole) {
       // launched as one item: the prefix's keys, then the siblings' own (PART_SIBLINGS)
       const int32_t nq = (int32_t)t->q_list.size() - q_pack;
       sib_items.push_back({q_pack, nq, (int32_t)t->kv_list.size(), (int32_t)(pre + nq), 0, 0, PART_SIBLINGS, (int32_t)(pre / KV_TILE)});
@@ -604,12 +609,11 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       std::copy_n(t->kv_list.begin() + kvoff[n0], pre, t->kv_list.begin() + (int64_t)at);
       for (int n : pk) t->kv_list.insert(t->kv_list.end(), node_slots[n].begin(), node_slots[n].end());
       if (t->kv_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "key lists exceed 2^31 entries");
-      sib_part.push_back(P);
     }
     for (int n : pk) {
       const int32_t q_off = (int32_t)t->q_list.size();
       for (int a = 0; a < t->seg_len[n]; ++a) t->q_list.push_back((int32_t)(t->row_off[n] + a));
-      merges.push_back({q_off, t->seg_len[n], P + rows, npref + 1});
+      (whole ? piece_merges : merges).push_back({q_off, t->seg_len[n], P + rows, npref + 1});
       FTask f;
       f.q_off = q_off;
       f.nq = t->seg_len[n];
@@ -619,6 +623,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       f.min_qpos = (int32_t)pre;
       f.part = P + npref * s.bmq + rows;
       f.cost = (double)f.nq * (double)f.nkv + 4096.0;
+      f.launched = !whole;
       ftasks.push_back(f);
       rows += t->seg_len[n];
     }
@@ -656,9 +661,18 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       }
     }
   }
-  if (part_rows > INT32_MAX / 2) return fail(PSATTN_E_UNSUPPORTED, "too many partial rows");
+  if (part_rows + piece_rows > INT32_MAX / 2) return fail(PSATTN_E_UNSUPPORTED, "too many partial rows");
   t->fwd_part_rows = part_rows;
+  t->piece_part_rows = piece_rows;
+  for (FTask& f : ftasks)
+    if (!f.launched) f.part += (int32_t)part_rows;
+  for (MergeEntry& m : piece_merges) m.part0 += (int32_t)part_rows;
+  t->merge_launch = merges;
+  t->max_merge_rows = 0;
+  for (const MergeEntry& m : merges) t->max_merge_rows = std::max(t->max_merge_rows, m.nq);
   t->merge = merges;
+  t->merge.insert(t->merge.end(), piece_merges.begin(), piece_merges.end());
+  std::vector<FwdItem> items;   // those launched
   {
     std::vector<double> c(ftasks.size());
     for (size_t i = 0; i < ftasks.size(); ++i) c[i] = ftasks[i].cost;
@@ -675,6 +689,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       for (int j = 0; j < n_chunks; ++j) {
         const int kvh = j % t->hkv, sub = j / t->hkv;
         t->fwd.push_back({f.q_off, f.nq, f.kv_off, f.nkv, f.kv_pos0, kvh * s.g + sub * s.hc, f.part, nfull});
+        if (f.launched) items.push_back(t->fwd.back());
       }
     }
   }
@@ -687,11 +702,6 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // kernels): an item's keys end at its last row, and one whose units all lie past the tile's last row
   // is not launched.
   t->siblings = !sib_items.empty();
-  std::vector<char> replaced(part_rows / s.bmq + 1, 0);   // by groups of bmq partial rows
-  for (int32_t P : sib_part) replaced[P / s.bmq] = replaced[P / s.bmq + 1] = 1;
-  std::vector<FwdItem> items;
-  for (const FwdItem& f : t->fwd)
-    if (f.part < 0 || !replaced[f.part / s.bmq]) items.push_back(f);
   for (const FwdItem& f : sib_items)
     for (int j = 0; j < n_chunks; ++j) {
       items.push_back(f);
@@ -713,13 +723,6 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   std::stable_sort(launch.begin(), launch.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
   t->fwd_launch.clear();
   for (const auto& l : launch) t->fwd_launch.push_back(items[l.second]);
-  t->merge_launch.clear();
-  t->max_merge_rows = 0;
-  for (const MergeEntry& m : t->merge) {
-    if (replaced[m.part0 / s.bmq]) continue;
-    t->merge_launch.push_back(m);
-    t->max_merge_rows = std::max(t->max_merge_rows, m.nq);
-  }
   std::vector<BkvItem> bkv_launch;
 
   // ---------------- dK/dV tasks: key tile x consumer-row chunk ----------------
@@ -1270,8 +1273,8 @@ psattn_status psattn_tree_get_info(const psattn_tree* t, psattn_tree_info* info)
   info->num_rows = t->Ns;
   info->unshared_tokens = t->Nu;
   info->visible_pairs = t->nvis;
-  info->fwd_items = (int64_t)t->fwd.size();
-  info->fwd_merges = (int64_t)t->merge.size();
+  info->fwd_items = (int64_t)t->fwd_launch.size();
+  info->fwd_merges = (int64_t)t->merge_launch.size();
   info->bkv_items = (int64_t)t->bkv.size();
   info->bkv_reduces = (int64_t)t->reduce.size();
   info->pad_slots = (int64_t)t->pad_slots.size();

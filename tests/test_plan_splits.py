@@ -93,3 +93,37 @@ def test_launched_items_cover_the_mask(hq, hkv, dtype, opts):
     cover = _launch_cover(wl, t, dtype == "bf16")
     assert all(n == 1 for n in cover.values())
     assert {(r, k) for _, r, k in cover} == _visible_pairs(wl.tree) and len(cover) == len(_visible_pairs(wl.tree)) * hq
+
+
+@pytest.mark.parametrize("parent,seg,hq,hkv,dtype", [
+    ([-1] + [0] * 256, [4096] + [16] * 256, 32, 8, "bf16"), ([-1] + [0] * 1200, [512] + [30] * 1200, 32, 8, "bf16"),
+    ([-1] + [0] * 40, [260] + [9] * 40, 10, 2, "bf16"), ([-1] + [0] * 64, [300] + [7] * 64, 4, 2, "fp32")])
+def test_unsplit_packs_take_no_workspace(parent, seg, hq, hkv, dtype):
+    """Packs of short siblings on whole prefixes write their results directly: no partial rows, no merges, no
+    forward workspace, and a backward that holds the row statistics and the dK/dV partial tiles alone."""
+    wl = W.custom(parent, seg, list(range(1, len(seg))), hq=hq, hkv=hkv, dtype=dtype, tensors=False)
+    t = P.Tree.from_workload(wl, opts={"fwd_kv_split": -1})
+    launch = t.plan_array("fwd_launch")
+    assert (launch[:, 6] == -2).any() and not (launch[:, 6] >= 0).any()
+    assert t.workspace_size(0) == 0 and t.info["fwd_partial_rows"] == 0
+    assert t.info["fwd_items"] == len(launch) and t.info["fwd_merges"] == 0 == len(t.plan_array("merge_launch"))
+    need = 4 * sum(seg) * hq * 4 + t.info["bkv_partial_tiles"] * 128 * wl.d * 8
+    assert t.workspace_size(1) <= need + 8 * 256
+
+
+def test_many_short_branches_fit_the_noalloc_array():
+    wl = W.make("c2-small", tensors=False)
+    t = P.Tree.from_workload(wl)
+    assert t.workspace_size(0) == 0 and t.workspace_size(1) <= P.NOALLOC_SCRATCH_MIB << 20
+
+
+@pytest.mark.parametrize("opts", [{}, {"fwd_kv_split": 64}, {"fwd_kv_split": -1}])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_every_partial_row_is_of_a_launched_tile(name, opts):
+    """The workspace holds the launched pieces' rows and nothing else: every tile of q_tile_rows that it has
+    belongs to one."""
+    parent, seg, samples, hq, hkv = SHAPES[name]
+    t = P.Tree.from_workload(W.custom(parent, seg, samples, hq=hq, hkv=hkv, tensors=False), opts=opts)
+    bmq, f = t.info["q_tile_rows"], t.plan_array("fwd_launch")
+    tiles = {int(p) // bmq for p in f[f[:, 6] >= 0, 6]}
+    assert tiles == set(range(t.info["fwd_partial_rows"] // bmq))
