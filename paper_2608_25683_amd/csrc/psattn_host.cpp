@@ -398,32 +398,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       }
   }
 
-  // per-node path slot list: slots of sequence positions 0 .. off+len-1
-  std::vector<int64_t> kvoff(N);
-  t->kv_list.clear();
   std::vector<int64_t> desc_rows(N, 0);   // rows of the (internal) descendants of each node
   for (int n = N - 1; n >= 0; --n)
     if (t->parent[n] >= 0) desc_rows[t->parent[n]] += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
-  {
-    // room for every list up front (address space; only what is written is touched): the paths, the packed
-    // siblings' prefixes (two siblings or more each), and the tiles' and consumers' rows
-    int64_t keys = 0, rows = 2 * t->Ns;
-    for (int n = 0; n < N; ++n) {
-      keys += t->off[n] + t->seg_len[n];
-      if (!t->ext[n] && 2 * t->seg_len[n] <= s.bmq) keys += t->off[n] / 2 + t->seg_len[n];
-      rows += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
-    }
-    t->kv_list.reserve((size_t)std::min<int64_t>(keys, INT32_MAX));
-    t->q_list.reserve((size_t)std::min<int64_t>(rows, INT32_MAX));
-  }
-  for (int n = 0; n < N; ++n) {
-    std::vector<int> path;
-    for (int m = n; m >= 0; m = t->parent[m]) path.push_back(m);
-    std::reverse(path.begin(), path.end());
-    kvoff[n] = (int64_t)t->kv_list.size();
-    for (int m : path) t->kv_list.insert(t->kv_list.end(), node_slots[m].begin(), node_slots[m].end());
-    if (t->kv_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "key lists exceed 2^31 entries");
-  }
 
   // ---------------- forward / dQ tasks: query tile x key range (pieces) ----------------
   struct FTask { int32_t q_off, nq, kv_off, kv_pos0, nkv, min_qpos, part; double cost; bool launched = true; };
@@ -571,13 +548,47 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     }
     cap_tiles = best_cap;
   }
+
+  // Key lists: of each node its path, the slots of sequence positions 0 .. off+len-1, or of a pack on an unsplit prefix
+  // the prefix and then every sibling's own keys (nothing reads such a sibling's path on its own).  Node n's
+  // own keys are at kvoff[n] + off[n] either way.
+  std::vector<int64_t> kvoff(N);
+  std::vector<int> whole_pack(N, -1);
+  for (size_t i = 0; i < packs.size(); ++i)
+    if (num_pieces(t->off[packs[i][0]]) == 1)
+      for (int n : packs[i]) whole_pack[n] = (int)i;
+  {
+    // room for the lists up front (address space; only what is written is touched)
+    int64_t keys = 0, rows = t->Ns;
+    for (int n = 0; n < N; ++n) {
+      keys += (whole_pack[n] < 0 || packs[whole_pack[n]][0] == n ? t->off[n] : 0) + t->seg_len[n];
+      rows += desc_rows[n] + (t->ext[n] ? 0 : t->seg_len[n]);
+    }
+    if (keys > INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "key lists exceed 2^31 entries");
+    t->kv_list.clear();
+    t->kv_list.reserve((size_t)keys);
+    t->q_list.reserve((size_t)std::min<int64_t>(rows, INT32_MAX));
+  }
+  for (int n = 0; n < N; ++n) {
+    if (whole_pack[n] >= 0 && packs[whole_pack[n]][0] != n) continue;   // with its pack's first sibling
+    std::vector<int> path;
+    for (int m = t->parent[n]; m >= 0; m = t->parent[m]) path.push_back(m);
+    for (size_t i = path.size(); i-- > 0;) t->kv_list.insert(t->kv_list.end(), node_slots[path[i]].begin(), node_slots[path[i]].end());
+    auto own = [&](int m) {
+      kvoff[m] = (int64_t)t->kv_list.size() - t->off[m];
+      t->kv_list.insert(t->kv_list.end(), node_slots[m].begin(), node_slots[m].end());
+    };
+    if (whole_pack[n] < 0) own(n);
+    else for (int m : packs[whole_pack[n]]) own(m);
+  }
+
   std::vector<FwdItem> sib_items;   // the launched items of unsplit packs (head0 per chunk)
   for (const std::vector<int>& pk : packs) {
     const int n0 = pk[0];
     const int64_t pre = t->off[n0];   // the common prefix: every sibling starts at the same position
     const int npref = num_pieces(pre);
     const int64_t split_keys = piece_keys(pre);
-    const bool whole = npref == 1;
+    const bool whole = whole_pack[n0] >= 0;
     int64_t& rows_used = whole ? piece_rows : part_rows;
     const int32_t P = (int32_t)rows_used;
     rows_used += (int64_t)(npref + 1) * s.bmq;
@@ -603,16 +614,10 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     if (whole) {
       // launched as one item: the prefix's keys, then the siblings' own (PART_SIBLINGS)
       const int32_t nq = (int32_t)t->q_list.size() - q_pack;
-      sib_items.push_back({q_pack, nq, (int32_t)t->kv_list.size(), (int32_t)(pre + nq), 0, 0, PART_SIBLINGS, (int32_t)(pre / KV_TILE)});
-      const size_t at = t->kv_list.size();
-      t->kv_list.resize(at + (size_t)pre);
-      std::copy_n(t->kv_list.begin() + kvoff[n0], pre, t->kv_list.begin() + (int64_t)at);
-      for (int n : pk) t->kv_list.insert(t->kv_list.end(), node_slots[n].begin(), node_slots[n].end());
-      if (t->kv_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "key lists exceed 2^31 entries");
+      sib_items.push_back({q_pack, nq, (int32_t)kvoff[n0], (int32_t)(pre + nq), 0, 0, PART_SIBLINGS, (int32_t)(pre / KV_TILE)});
     }
     for (int n : pk) {
-      const int32_t q_off = (int32_t)t->q_list.size();
-      for (int a = 0; a < t->seg_len[n]; ++a) t->q_list.push_back((int32_t)(t->row_off[n] + a));
+      const int32_t q_off = q_pack + rows;
       (whole ? piece_merges : merges).push_back({q_off, t->seg_len[n], P + rows, npref + 1});
       FTask f;
       f.q_off = q_off;

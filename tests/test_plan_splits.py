@@ -111,6 +111,17 @@ def test_unsplit_packs_take_no_workspace(parent, seg, hq, hkv, dtype):
     assert t.workspace_size(1) <= need + 8 * 256
 
 
+@pytest.mark.parametrize("opts", [{}, {"fwd_kv_split": 64}, {"fwd_kv_split": -1}])
+@pytest.mark.parametrize("seg", [[512] + [30] * 120, [330, 16, 9, 30, 1, 16, 64], [4096] + [16] * 40])
+def test_key_lists_are_no_longer_than_the_paths(seg, opts):
+    """Packs share their siblings' lists and add none: what fits the 2^31 entries as paths fits in any plan."""
+    wl = W.custom([-1] + [0] * (len(seg) - 1), seg, list(range(1, len(seg))), hq=8, hkv=2, tensors=False)
+    t = P.Tree.from_workload(wl, opts=opts)
+    assert len(t.plan_array("kv_list")) <= seg[0] + sum(seg[0] + n for n in seg[1:])
+    rows = sum(seg)
+    assert len(t.plan_array("q_list")) <= 2 * rows + sum(seg[1:])   # tiles; consumers: every node's own and the root's
+
+
 def test_many_short_branches_fit_the_noalloc_array():
     wl = W.make("c2-small", tensors=False)
     t = P.Tree.from_workload(wl)
