@@ -37,6 +37,16 @@ def test_automatic_splits_are_equal_pieces():
         assert len(tiles) == nparts and tiles.max() - tiles.min() <= nparts
 
 
+def test_a_long_range_is_split_among_any_number_of_trees():
+    # a cached 300000-token prefix and 16 rows, among more one-token trees than the planner's bound on pieces
+    n = 66000
+    wl = W.custom([-1, 0] + [-1] * n, [300000, 16] + [1] * n, list(range(1, n + 2)), hq=2, hkv=1, d=64, tensors=False,
+                  block_policy=W.blocks_exact)
+    call, _ = W.call_subset(wl, list(range(1, n + 2)), [0])
+    f = P.Tree.from_workload(call).plan_array("fwd_launch")
+    assert f[:, 3].max() <= 32 * 64
+
+
 @pytest.mark.parametrize("hq,hkv,prefix,branches,seg", [(28, 4, 3434, 7, 928), (64, 8, 2048, 8, 1800), (40, 8, 1487, 12, 300)])
 def test_automatic_splits_stay_within_the_noalloc_array(hq, hkv, prefix, branches, seg):
     wl = W.custom([-1] + [0] * branches, [prefix] + [seg] * branches, list(range(1, branches + 1)), hq=hq, hkv=hkv,
