@@ -491,7 +491,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     return n;
   };
   if (o.fwd_kv_split == 0) {
-    // Automatic split of the key ranges: whole ranges, or pieces of at most 32, 24, .. 4 tiles,
+    // Automatic split of the key ranges: whole ranges, or pieces of at most 32, 24, .. 4 tiles (or 48 .. 512),
     // whichever the items' cost model expects to be over first on the compute units that one head
     // chunk gets.  A piece costs its start-up and its partial rows, written and read again by the
     // merge passes; a long range on an idle chip costs more (a 4096-token cached prefix and 48 new
@@ -512,7 +512,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     size_t whole_items = 0;
     double best = 0.0;
     int64_t best_cap = INT64_MAX;
-    for (int64_t cap : {INT64_MAX, (int64_t)32, (int64_t)24, (int64_t)16, (int64_t)12, (int64_t)8, (int64_t)6, (int64_t)4}) {
+    auto consider = [&](int64_t cap) {   // false: finer pieces are no better
       cap_tiles = cap;
       std::vector<double> c;
       double moved = 0.0;
@@ -541,16 +541,24 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
         }
       }
       if (cap == INT64_MAX) whole_items = c.size();
-      if (c.size() > whole_items + 65536) break;
-      if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(0, base_tiles) <= kNoallocBytes) break;
+      if (c.size() > whole_items + 65536) return false;
+      if (cap != INT64_MAX && bwd_bytes(prows, base_tiles) > kNoallocBytes && bwd_bytes(0, base_tiles) <= kNoallocBytes) return false;
       const double extra = (moved > 0 ? 2 * kMergeLaunch : 0.0) + moved / kMergeBytes;
-      if (cap != INT64_MAX && even_share(c, (double)num_cus / n_chunks) + extra >= kSplitGain * best) break;
+      if (cap != INT64_MAX && even_share(c, (double)num_cus / n_chunks) + extra >= kSplitGain * best) return false;
       const double time = makespan(c, (double)num_cus / n_chunks) + extra;
       if (cap == INT64_MAX || time < kSplitGain * best) {
         best = time;
         best_cap = cap;
       }
-    }
+      return true;
+    };
+    for (int64_t cap : {INT64_MAX, (int64_t)32, (int64_t)24, (int64_t)16, (int64_t)12, (int64_t)8, (int64_t)6, (int64_t)4})
+      if (!consider(cap)) break;
+    // Nothing that fine: 32 tiles a piece can be more partial rows than the array of psattn_bwd_noalloc holds, or more
+    // bytes than the pieces gain, where a few pieces of very long ranges are not (a sequence of 20016 rows, 2 heads
+    // on 1, d = 128: forward and dQ 401 and 540 us whole, 226 and 288 us in pieces, their merge and sum included).
+    if (best_cap == INT64_MAX)
+      for (int64_t cap : {(int64_t)48, (int64_t)64, (int64_t)96, (int64_t)128, (int64_t)192, (int64_t)256, (int64_t)512}) consider(cap);
     cap_tiles = best_cap;
   }
 

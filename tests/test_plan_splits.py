@@ -47,6 +47,13 @@ def test_a_long_range_is_split_among_any_number_of_trees():
     assert f[:, 3].max() <= 32 * 64
 
 
+def test_long_ranges_are_split_where_fine_pieces_do_not_fit():
+    # in pieces of 32 key tiles its partial rows would be more than the psattn_bwd_noalloc array holds
+    wl = W.custom([-1, 0], [20000, 16], [1], hq=2, hkv=1, tensors=False)
+    t = P.Tree.from_workload(wl)
+    assert t.plan_array("fwd_launch")[:, 3].max() <= 10000 and t.workspace_size(1) <= P.NOALLOC_SCRATCH_MIB << 20
+
+
 @pytest.mark.parametrize("hq,hkv,prefix,branches,seg", [(28, 4, 3434, 7, 928), (64, 8, 2048, 8, 1800), (40, 8, 1487, 12, 300)])
 def test_automatic_splits_stay_within_the_noalloc_array(hq, hkv, prefix, branches, seg):
     wl = W.custom([-1] + [0] * branches, [prefix] + [seg] * branches, list(range(1, branches + 1)), hq=hq, hkv=hkv,
