@@ -475,10 +475,12 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   int64_t chunk_rows = std::max<int64_t>(2048, total_b * t->hkv / std::max(1, num_cus) / BKV_TILE / Q_SUB * Q_SUB);
   if (o.bwd_q_chunk > 0) chunk_rows = ((int64_t)o.bwd_q_chunk + Q_SUB - 1) / Q_SUB * Q_SUB;
   else if (o.bwd_q_chunk < 0) chunk_rows = INT64_MAX;
-  // rows per chunk of a row list: as asked for, or equal chunks of at most chunk_rows
+  // rows per chunk of a row list: as asked for, or equal chunks of at most chunk_rows (full ones and a rest
+  // where even_chunks is off)
+  bool even_chunks = o.bwd_q_chunk <= 0;
   auto list_chunk = [&](int64_t nq, int64_t cap) -> int64_t {
     if (nq <= cap) return nq;
-    if (o.bwd_q_chunk > 0) return cap;
+    if (!even_chunks) return cap;
     const int64_t n = (nq + cap - 1) / cap;
     return ((nq + n - 1) / n + Q_SUB - 1) / Q_SUB * Q_SUB;
   };
@@ -771,12 +773,17 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     // expects to be over first on the compute units that one kv head gets.  A chunk costs its start-up
     // and a partial tile, written and read again; a list that one unit works through alone costs more
     // (a 512-token prompt and 8 branches of 96 rows: 96 items on 256 units, the longest 160 steps,
-    // 221 us).
-    const int64_t coarse = chunk_rows;
+    // 221 us).  The coarse chunks are equal ones, or full ones and a rest: few more equal chunks than compute units
+    // are two rounds, where the rests fill the units that the full ones leave (a 6000-token prompt and 64 branches of 300
+    // rows, 2 heads on 1, d = 128: 282 equal chunks on 256 units 415 us, 235 full ones and 47 rests 309 us).
+    const int64_t coarse = chunk_rows, coarse_tiles = part_tiles_of(coarse);
+    const bool bounded = bwd_bytes(part_rows, coarse_tiles) <= kNoallocBytes;   // a finer one has to fit the array too
     double best = 0.0;
-    for (int64_t cap : {coarse, (int64_t)1024, (int64_t)512, (int64_t)384, (int64_t)256, (int64_t)192, (int64_t)128, (int64_t)96,
-                        (int64_t)64, (int64_t)32}) {
-      if (cap > coarse) continue;
+    bool best_even = true;
+    enum { GOOD, NO_GAIN, NO_ROOM };
+    auto consider = [&](int64_t cap, bool even) {   // NO_GAIN, NO_ROOM: finer chunks neither
+      const bool first = cap == coarse && even;
+      even_chunks = even;
       std::vector<double> c;
       double moved = 0.0;
       int64_t ptiles = 0;
@@ -793,18 +800,26 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
           ptiles += (int64_t)parts * t->hkv;
         }
       }
-      if (c.size() > 65536) break;
-      if (cap != coarse && bwd_bytes(part_rows, ptiles) > kNoallocBytes &&
-          bwd_bytes(part_rows, part_tiles_of(coarse)) <= kNoallocBytes)
-        break;
+      if (c.size() > 65536) return NO_GAIN;
+      if (!first && bounded && bwd_bytes(part_rows, ptiles) > kNoallocBytes) return NO_ROOM;
       const double extra = (ptiles ? kMergeLaunch : 0.0) + moved / kMergeBytes;
-      if (cap != coarse && even_share(c, (double)num_cus / t->hkv) + extra >= kSplitGain * best) break;
+      if (cap != coarse && even_share(c, (double)num_cus / t->hkv) + extra >= kSplitGain * best) return NO_GAIN;
       const double time = makespan(c, (double)num_cus / t->hkv) + extra;
-      if (cap == coarse || time < kSplitGain * best) {
+      if (first || time < kSplitGain * best) {
         best = time;
         chunk_rows = cap;
+        best_even = even;
       }
-    }
+      return GOOD;
+    };
+    auto st = consider(coarse, true);
+    if (st == GOOD && coarse_tiles) consider(coarse, false);
+    for (int64_t cap : {1024, 512, 384, 256, 192, 128, 96, 64, 32})
+      if (st == GOOD && cap <= coarse) st = consider(cap, true);
+    if (st == NO_ROOM && chunk_rows == coarse)   // (more than the array of psattn_bwd_noalloc holds)
+      for (int64_t cap : {1536, 2048, 3072, 4096})
+        if (cap < coarse) consider(cap, true);
+    even_chunks = best_even;
   }
   struct BTask {
     int32_t kv_off, nk, kv_pos0, q_off, nq, mask_lo, mask_hi, part_base, nparts, chunk, acc;

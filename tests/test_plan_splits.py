@@ -54,6 +54,17 @@ def test_long_ranges_are_split_where_fine_pieces_do_not_fit():
     assert t.plan_array("fwd_launch")[:, 3].max() <= 10000 and t.workspace_size(1) <= P.NOALLOC_SCRATCH_MIB << 20
 
 
+def test_chunks_of_consumer_rows_fill_the_compute_units():
+    # 47 key tiles whose even share of 256 units is 5 and a bit: 6 equal chunks each would be a second round of
+    # a few; longest first over the units, the end is within an eighth of the even share
+    wl = W.custom([-1] + [0] * 64, [6000] + [300] * 64, list(range(1, 65)), hq=2, hkv=1, tensors=False)
+    rows = sorted((int(n) for n in P.Tree.from_workload(wl).plan_array("bkv_items")[:, 4]), reverse=True)
+    units = [0] * 256
+    for n in rows:
+        units[units.index(min(units))] += n
+    assert max(units) <= 1.125 * sum(rows) / 256
+
+
 @pytest.mark.parametrize("hq,hkv,prefix,branches,seg", [(28, 4, 3434, 7, 928), (64, 8, 2048, 8, 1800), (40, 8, 1487, 12, 300)])
 def test_automatic_splits_stay_within_the_noalloc_array(hq, hkv, prefix, branches, seg):
     wl = W.custom([-1] + [0] * branches, [prefix] + [seg] * branches, list(range(1, branches + 1)), hq=hq, hkv=hkv,
