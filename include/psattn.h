@@ -347,7 +347,8 @@ psattn_status psattn_tree_get_info(const psattn_tree* tree, psattn_tree_info* in
  *   9 q_pos                   sequence position of each q_list entry
  *  10 fwd_launch [n][8]       the forward items as launched, in launch order: those with rows; packed
  *                             siblings on an unsplit prefix as one item (part -2) of the prefix's keys
- *                             and then the siblings' own, in the order of its rows
+ *                             and then the siblings' own, in the order of its rows.  bf16: an item holds 8
+ *                             (32-row subtile, query head) units of its tile; nkv and nfull are what those see
  *  11 merge_launch [n][4]     the merge records that the launched items need
  * *data stays valid until psattn_tree_destroy. */
 psattn_status psattn_tree_plan_array(const psattn_tree* tree, int which, const int32_t** data,

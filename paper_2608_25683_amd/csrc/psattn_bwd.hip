@@ -656,13 +656,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const ItemUnits un = item_units<SIB>(a.s, a.plan, it);
+  const ItemUnits un = item_units<SIB>(a.s, it);
   const int hk = un.hk;
   const int nkv = un.nkv;
   const int* kvl = a.plan.kv_list + it.kv_off;
   const int ntiles = (nkv + KV_TILE - 1) / KV_TILE;
 
-  for (int i = tid; i < IDX_BLK; i += NW * 64) {   // (it.nkv: known before the item's own range)
+  for (int i = tid; i < IDX_BLK; i += NW * 64) {
     s_slot[0][i] = kvl[min(i, it.nkv - 1)];
     if (it.nkv > IDX_BLK) s_slot[1][i] = kvl[min(IDX_BLK + i, it.nkv - 1)];
   }
@@ -942,7 +942,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
           t * KV_TILE + 32, masked, kcopies, Flag<true>{});
   };
   int t = 0;
-  for (; t < min(un.nfull, ntiles); ++t) tile(t, Flag<false>{});
+  for (; t < it.nfull; ++t) tile(t, Flag<false>{});
   for (; t < ntiles; ++t) tile(t, Flag<true>{});
   // the last stage's S and dP MFMAs (of the block past the end) have no readers: their registers
   // may be reused at once, so let them finish first (scheduling barriers keep the epilogue's

@@ -279,7 +279,6 @@ struct ItemUnits {
   int hk;      // kv head
   int u0;      // first unit
   int nkv;     // keys of the item's range that some of its rows see (at least 1)
-  int nfull;   // leading key tiles that all of its rows see whole
   // subtile of unit u0 + i, and its query head
   __device__ __forceinline__ int subtile(const Shape& s, int i, int& head) const {
     const int st = (u0 + i) / s.g;
@@ -288,20 +287,12 @@ struct ItemUnits {
   }
 };
 template <bool SIB>
-__device__ __forceinline__ ItemUnits item_units(const Shape& s, const PlanView& plan, const FwdItem& it) {
+__device__ __forceinline__ ItemUnits item_units(const Shape& s, const FwdItem& it) {
   ItemUnits u;
   u.hk = it.head0 / s.g;
   u.u0 = (it.head0 - u.hk * s.g) / s.hc * 8;
-  const int r0 = u.u0 / s.g * 32, r1 = min(it.nq, ((u.u0 + 7) / s.g + 1) * 32) - 1;   // first and last row
-  if (SIB && it.part == PART_SIBLINGS) {
-    u.nkv = it.nkv - it.nq + r1 + 1;
-    u.nfull = (it.nkv - it.nq) / KV_TILE;
-    return u;
-  }
-  // a tile's rows have ascending positions, or all lie past the range (packed siblings' prefix)
-  const int* pos = plan.q_pos + it.q_off;
-  u.nkv = max(1, min(it.nkv, pos[r1] + 1 - it.kv_pos0));
-  u.nfull = max(0, min(u.nkv, pos[r0] + 1 - it.kv_pos0)) / KV_TILE;
+  u.nkv = it.nkv;   // (the planner's, but an item of packed siblings holds every row's own key)
+  if (SIB && it.part == PART_SIBLINGS) u.nkv += min(it.nq, ((u.u0 + 7) / s.g + 1) * 32) - it.nq;
   return u;
 }
 

@@ -333,6 +333,7 @@ psattn_status check_plan(const psattn_tree* t) {
     if (f.head0 < 0 || f.head0 + s.hc > s.hq) return bad("launched item heads", (int64_t)i);
     if (f.part < PART_SIBLINGS || (f.part >= 0 && (int64_t)f.part + f.nq > t->fwd_part_rows)) return bad("launched item partial rows", (int64_t)i);
     if (f.part == PART_SIBLINGS && f.nkv < f.nq) return bad("launched sibling keys", (int64_t)i);
+    if (f.nfull < 0 || (int64_t)f.nfull * KV_TILE > f.nkv) return bad("launched item unmasked tiles", (int64_t)i);
   }
   auto check_merge = [&](const MergeEntry& m, int64_t rows, size_t i) {
     if (m.nq < 1 || m.q_off < 0 || (int64_t)m.q_off + m.nq > nql) return bad("merge rows", (int64_t)i);
@@ -719,8 +720,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   // short items and ran on alone: 568 items of up to 36 tiles took 198 us, 124 us of them busy).
   // The head chunks of a task have one key and stay in order.
   // bf16 items hold 8 (subtile, head) units of their tile, subtile by subtile (item_units in the
-  // kernels): an item's keys end at its last row, and one whose units all lie past the tile's last row
-  // is not launched.
+  // kernels): an item's keys end at its last row, its unmasked tiles at what its first row sees, and one whose
+  // units all lie past the tile's last row is not launched.  The launched record holds these limits, so that a
+  // workgroup reads nothing between its record and its first tile.
   t->siblings = !sib_items.empty();
   for (const FwdItem& f : sib_items)
     for (int j = 0; j < n_chunks; ++j) {
@@ -729,14 +731,20 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     }
   std::vector<std::pair<int64_t, int>> launch;   // (key tiles, item)
   for (size_t i = 0; i < items.size(); ++i) {
-    const FwdItem& f = items[i];
+    FwdItem& f = items[i];
     int64_t keys = f.nkv;
     if (bf16) {
-      const int u0 = f.head0 % s.g / s.hc * 8;
-      if (u0 / s.g * Q_SUB >= f.nq) continue;
+      const int u0 = f.head0 % s.g / s.hc * 8, first = u0 / s.g * Q_SUB;
+      if (first >= f.nq) continue;
       const int last = std::min<int>(f.nq, ((u0 + 7) / s.g + 1) * Q_SUB) - 1;
+      // keys of the range that row r sees (a tile's rows have ascending positions, or all lie past the range)
+      auto seen = [&](int r) { return std::min<int64_t>(f.nkv, (int64_t)t->row_pos[t->q_list[f.q_off + r]] + 1 - f.kv_pos0); };
       if (f.part == PART_SIBLINGS) keys = f.nkv - f.nq + last + 1;
-      else keys = std::max<int64_t>(1, std::min<int64_t>(f.nkv, (int64_t)t->row_pos[t->q_list[f.q_off + last]] + 1 - f.kv_pos0));
+      else {
+        keys = std::max<int64_t>(1, seen(last));
+        f.nfull = (int32_t)(std::max<int64_t>(0, seen(first)) / KV_TILE);
+        f.nkv = (int32_t)keys;
+      }
     }
     launch.push_back({(keys + KV_TILE - 1) / KV_TILE, (int)i});
   }

@@ -31,11 +31,13 @@ struct FwdItem {     // also the dQ item
   int32_t q_off;     // first entry in q_list (packed row indices)
   int32_t nq;        // rows in the tile, 1..q_tile_rows
   int32_t kv_off;    // entry in kv_list holding the slot of the first key
-  int32_t nkv;       // keys in this item's range, >= 1
+  int32_t nkv;       // keys in this item's range, >= 1 (launched bf16 items: that some of its rows see)
   int32_t kv_pos0;   // sequence position of the first key
-  int32_t head0;     // first query head of the chunk
-  int32_t part;      // -1: write final results; PART_SIBLINGS: likewise (below); else first partial row
-  int32_t nfull;     // leading key tiles that need no mask
+  int32_t head0;     // kv head and chunk: query head hk * G + chunk * hc.  In the plan's list the item is rows x
+                     //   heads head0 .. head0 + hc - 1; a launched bf16 item holds units 8 chunk .. 8 chunk + 7 of
+                     //   the tile's (32-row subtile, query head of hk) units, counted subtile by subtile
+  int32_t part;      // -1: write final results; PART_SIBLINGS: likewise (above); else first partial row
+  int32_t nfull;     // leading key tiles that need no mask (launched bf16 items: for its own rows)
 };
 
 struct MergeEntry {  // a query tile whose key range was split into pieces

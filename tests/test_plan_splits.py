@@ -166,3 +166,20 @@ def test_every_partial_row_is_of_a_launched_tile(name, opts):
     bmq, f = t.info["q_tile_rows"], t.plan_array("fwd_launch")
     tiles = {int(p) // bmq for p in f[f[:, 6] >= 0, 6]}
     assert tiles == set(range(t.info["fwd_partial_rows"] // bmq))
+
+
+@pytest.mark.parametrize("opts", [{}, {"fwd_kv_split": 64}, {"fwd_kv_split": -1}])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (5, 1), (2, 2), (7, 1), (12, 2)])
+def test_launched_items_carry_their_limits(hq, hkv, opts):
+    """A launched bf16 item's keys end at the last that one of its rows sees, and its unmasked tiles are all those
+    that every one of its rows sees whole."""
+    wl = W.custom([-1, 0, 0, 1], [300, 161, 33, 90], [2, 3], hq=hq, hkv=hkv, tensors=False)
+    t = P.Tree.from_workload(wl, opts=opts)
+    G, hc, q_pos = hq // hkv, t.info["head_chunk"], t.plan_array("q_pos")
+    for q_off, nq, _, nkv, kv_pos0, head0, part, nfull in t.plan_array("fwd_launch"):
+        assert part != -2
+        u0 = head0 % G // hc * 8
+        rows = [r for i in range(8) for r in range(32 * ((u0 + i) // G), min(nq, 32 * ((u0 + i) // G) + 32))]
+        seen = [int(q_pos[q_off + r]) + 1 - kv_pos0 for r in rows]
+        assert nkv == max(1, min(nkv, max(seen)))
+        assert nfull == max(0, min(nkv, min(seen))) // 64
