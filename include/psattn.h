@@ -350,6 +350,7 @@ psattn_status psattn_tree_get_info(const psattn_tree* tree, psattn_tree_info* in
  *                             and then the siblings' own, in the order of its rows.  bf16: an item holds 8
  *                             (32-row subtile, query head) units of its tile; nkv and nfull are what those see
  *  11 merge_launch [n][4]     the merge records that the launched items need
+ *  12 bkv_launch [n][10]      the dK/dV items in launch order
  * *data stays valid until psattn_tree_destroy. */
 psattn_status psattn_tree_plan_array(const psattn_tree* tree, int which, const int32_t** data,
                                      int64_t* count, int32_t* width);

@@ -69,8 +69,9 @@ struct psattn_tree {
   int64_t fwd_part_rows = 0, bkv_part_tiles = 0;
   int64_t piece_part_rows = 0;      // partial rows that only the independent pieces have, behind fwd_part_rows
   int32_t max_merge_rows = 0, siblings = 0;
-  // the forward / dQ items and merge records of the device image (see build_plan)
+  // the forward / dQ items, merge records and dK/dV items of the device image (see build_plan)
   std::vector<FwdItem> fwd_launch;
+  std::vector<BkvItem> bkv_launch;
   std::vector<MergeEntry> merge_launch;
   // device image of the plan
   size_t o_row_pos = 0, o_row_slot = 0, o_q = 0, o_qpos = 0, o_kv = 0, o_fwd = 0, o_merge = 0, o_bkv = 0, o_reduce = 0, o_pad = 0;
@@ -345,8 +346,9 @@ psattn_status check_plan(const psattn_tree* t) {
     if (check_merge(t->merge[i], t->fwd_part_rows + t->piece_part_rows, i) != PSATTN_OK) return PSATTN_E_INTERNAL;
   for (size_t i = 0; i < t->merge_launch.size(); ++i)
     if (check_merge(t->merge_launch[i], t->fwd_part_rows, i) != PSATTN_OK) return PSATTN_E_INTERNAL;
-  for (size_t i = 0; i < t->bkv.size(); ++i) {
-    const BkvItem& b = t->bkv[i];
+  if (t->bkv.size() != t->bkv_launch.size()) return bad("dK/dV items launched", (int64_t)t->bkv_launch.size());
+  for (size_t i = 0; i < 2 * t->bkv.size(); ++i) {   // as listed, then as launched
+    const BkvItem& b = i < t->bkv.size() ? t->bkv[i] : t->bkv_launch[i - t->bkv.size()];
     if (b.nk < 1 || b.nk > BKV_TILE || b.kv_off < 0 || (int64_t)b.kv_off + b.nk > nkl) return bad("dK/dV item keys", (int64_t)i);
     if (b.nq < 1 || b.q_off < 0 || (int64_t)b.q_off + b.nq > nql) return bad("dK/dV item rows", (int64_t)i);
     if (b.hk < 0 || b.hk >= s.hkv) return bad("dK/dV item kv head", (int64_t)i);
@@ -751,7 +753,6 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   std::stable_sort(launch.begin(), launch.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
   t->fwd_launch.clear();
   for (const auto& l : launch) t->fwd_launch.push_back(items[l.second]);
-  std::vector<BkvItem> bkv_launch;
 
   // ---------------- dK/dV tasks: key tile x consumer-row chunk ----------------
   // consumer list of node m: every row of every (internal) descendant (node order), then m's own
@@ -928,7 +929,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       if (btasks[x].steps != btasks[y].steps) return btasks[x].steps > btasks[y].steps;
       return btasks[x].group < btasks[y].group;
     });
-    emit(bkv_launch);
+    emit(t->bkv_launch);
   }
 
   // ---------------- slots of this call's blocks that hold no token ----------------
@@ -964,7 +965,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   t->o_kv = place(t->kv_list.size() * 4);
   t->o_fwd = place(t->fwd_launch.size() * sizeof(FwdItem));
   t->o_merge = place(t->merge_launch.size() * sizeof(MergeEntry));
-  t->o_bkv = place(t->bkv.size() * sizeof(BkvItem));
+  t->o_bkv = place(t->bkv_launch.size() * sizeof(BkvItem));
   t->o_reduce = place(t->reduce.size() * sizeof(ReduceEntry));
   t->o_pad = place(t->pad_slots.size() * 4);
   t->plan_bytes = cur;
@@ -980,7 +981,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   put(t->o_kv, t->kv_list.data(), t->kv_list.size() * 4);
   put(t->o_fwd, t->fwd_launch.data(), t->fwd_launch.size() * sizeof(FwdItem));
   put(t->o_merge, t->merge_launch.data(), t->merge_launch.size() * sizeof(MergeEntry));
-  put(t->o_bkv, bkv_launch.data(), t->bkv.size() * sizeof(BkvItem));
+  put(t->o_bkv, t->bkv_launch.data(), t->bkv_launch.size() * sizeof(BkvItem));
   put(t->o_reduce, t->reduce.data(), t->reduce.size() * sizeof(ReduceEntry));
   put(t->o_pad, t->pad_slots.data(), t->pad_slots.size() * 4);
   return PSATTN_OK;
@@ -1210,7 +1211,7 @@ psattn_status psattn_bwd(const psattn_tree* t, const void* Q, const void* K, con
   a.n_merge = (int32_t)t->merge_launch.size();
   a.max_merge_rows = t->max_merge_rows;
   a.siblings = t->siblings;
-  a.n_bkv = (int32_t)t->bkv.size();
+  a.n_bkv = (int32_t)t->bkv_launch.size();
   a.n_reduce = (int32_t)t->reduce.size();
   a.n_pad = (int32_t)t->pad_slots.size();
   a.Q = Q;
@@ -1345,6 +1346,7 @@ psattn_status psattn_tree_plan_array(const psattn_tree* t, int which, const int3
     case 9: *data = t->q_pos.data(); *count = (int64_t)t->q_pos.size(); *width = 1; break;
     case 10: *data = (const int32_t*)t->fwd_launch.data(); *count = (int64_t)t->fwd_launch.size(); *width = 8; break;
     case 11: *data = (const int32_t*)t->merge_launch.data(); *count = (int64_t)t->merge_launch.size(); *width = 4; break;
+    case 12: *data = (const int32_t*)t->bkv_launch.data(); *count = (int64_t)t->bkv_launch.size(); *width = 10; break;
     default: return fail(PSATTN_E_INVALID_ARG, "unknown plan array %d", which);
   }
   return PSATTN_OK;

@@ -11,6 +11,7 @@ from test_abi_host import _check_plan, _visible_pairs  # noqa: E402
 
 SHAPES = {   # name -> (parent, seg, samples, hq, hkv): what the automatic rules split
     "long_range": ([-1, 0], [700, 20], [1], 8, 2),            # key ranges of few row tiles
+    "longer_range": ([-1, 0, 0], [1600, 40, 33], [1, 2], 5, 1),
     "few_branches": ([-1, 0, 0, 0], [260, 70, 33, 5], [1, 2, 3], 4, 2),
     "one_head": ([-1, 0, 0], [400, 130, 129], [1, 2], 5, 1),
     "short_siblings": ([-1] + [0] * 6, [330, 16, 9, 30, 1, 16, 64], list(range(1, 7)), 8, 2),
@@ -24,7 +25,10 @@ def test_automatic_splits_cover_the_mask(name, dtype):
     wl = W.custom(parent, seg, samples, hq=hq, hkv=hkv, dtype=dtype, tensors=False)
     t = P.Tree.from_workload(wl)
     assert t.info["bkv_reduces"] > 0
+    if "long" in name:   # key ranges in pieces, too
+        assert len(t.plan_array("merge_launch")) > 0
     _check_plan(wl, t)
+    _check_cover(wl, t, dtype == "bf16")
 
 
 def test_automatic_splits_are_equal_pieces():
@@ -75,10 +79,11 @@ def test_automatic_splits_stay_within_the_noalloc_array(hq, hkv, prefix, branche
     assert P.Tree.from_workload(wl).workspace_size(1) <= limit
 
 
-def _launch_cover(wl, t, bf16):
-    """(head, row, key row) -> times covered, from the launched items as the kernels read them."""
+def _launch_cover(wl, t, bf16, cached=None):
+    """(head, row, key row) -> times covered, from the launched items as the kernels read them (cached: slot -> key
+    row of keys that are no rows of the call)."""
     G, hc = wl.hq // wl.hkv, t.info["head_chunk"]
-    slot_to_row = {int(s): r for r, s in enumerate(wl.tree.row_slots())}
+    slot_to_row = {**(cached or {}), **({int(s): r for r, s in enumerate(wl.tree.row_slots())})}
     q_list, kv_list, q_pos = t.plan_array("q_list"), t.plan_array("kv_list"), t.plan_array("q_pos")
     cover, written = {}, set()
     for q_off, nq, kv_off, nkv, kv_pos0, head0, part, _ in t.plan_array("fwd_launch"):
@@ -109,6 +114,17 @@ def _launch_cover(wl, t, bf16):
     return cover
 
 
+def _check_cover(wl, t, bf16):
+    """The launched items cover every visible pair of a row of the call once per query head, and the launched
+    dK/dV items are the listed ones in another order."""
+    cover = _launch_cover(wl, t, bf16)
+    visible = {(r, k) for r, k in _visible_pairs(wl.tree) if r >= 0}
+    assert all(n == 1 for n in cover.values())
+    assert {(r, k) for _, r, k in cover} == visible and len(cover) == len(visible) * wl.hq
+    listed, launched = (sorted(map(tuple, t.plan_array(a))) for a in ("bkv_items", "bkv_launch"))
+    assert listed == launched
+
+
 @pytest.mark.parametrize("opts", [{}, {"fwd_kv_split": 64}, {"fwd_kv_split": -1}])
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("hq,hkv", [(8, 2), (5, 1), (2, 2), (8, 1), (7, 1), (12, 2)])
@@ -118,9 +134,27 @@ def test_launched_items_cover_the_mask(hq, hkv, dtype, opts):
     t = P.Tree.from_workload(wl, opts=opts)
     if opts.get("fwd_kv_split", 0) <= 0:
         assert (t.plan_array("fwd_launch")[:, 6] == -2).any()
-    cover = _launch_cover(wl, t, dtype == "bf16")
-    assert all(n == 1 for n in cover.values())
-    assert {(r, k) for _, r, k in cover} == _visible_pairs(wl.tree) and len(cover) == len(_visible_pairs(wl.tree)) * hq
+    _check_cover(wl, t, dtype == "bf16")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_siblings_under_a_cached_prefix(dtype):
+    # packed siblings whose prefix an earlier call computed: as one item, and with the prefix in pieces
+    forest = W.custom([-1] + [0] * 6, [330, 16, 9, 14, 1, 12, 16], list(range(1, 7)), hq=8, hkv=2, dtype=dtype, tensors=False)
+    call, rows = W.call_subset(forest, list(range(1, 7)), [0])
+    for opts, whole in (({"fwd_kv_split": -1}, True), ({"fwd_kv_split": 128}, False)):
+        t = P.Tree.from_workload(call, opts=opts)
+        assert (t.plan_array("fwd_launch")[:, 6] == -2).any() == whole == (len(t.plan_array("merge_launch")) == 0)
+        cover = _launch_cover(call, t, dtype == "bf16", cached={int(s): -1 - i for i, s in enumerate(_cached_slots(forest, 0))})
+        # forest rows: the cached node's are its first 330
+        want = {(r, k) for r, k in _visible_pairs(forest.tree) if r >= 330}
+        got = {(int(rows[r]), -1 - k if k < 0 else int(rows[k])) for _, r, k in cover}
+        assert got == want and all(n == 1 for n in cover.values()) and len(cover) == len(want) * forest.hq
+
+
+def _cached_slots(wl, node):
+    tr = wl.tree
+    return [s for b in range(tr.blk_ptr[node], tr.blk_ptr[node + 1]) for s in range(tr.blk_base[b], tr.blk_base[b] + tr.blk_len[b])]
 
 
 @pytest.mark.parametrize("parent,seg,hq,hkv,dtype", [
