@@ -55,7 +55,7 @@ __device__ __forceinline__ void sincos_reduced(double x, float& sf, float& cf) {
 template <bool BF16>
 __global__ __launch_bounds__(256) void rope_kernel(PlanView plan, int32_t ns, int32_t heads, int32_t d, double log2_theta,
                                                    double sign, void* X) {
-  __shared__ float s_sin[256], s_cos[256];
+  __shared__ __attribute__((aligned(16))) float s_sin[256], s_cos[256];   // (read 16 bytes at a time)
   const int half = d / 2, rows = 256 / half;
   const int row0 = blockIdx.x * rows;
   {
