@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // ============================================================================================
 // dK/dV: workgroup (i, y) takes keys 32 y .. 32 y + 31 of BkvItem i; wave w takes the steps (32-row
 // subtile, head of the group) w, w + 4, ...  K and V of the keys are in LDS (the B operands of
-// S = Q K^T and dP = dO V^T); the rows of Q and dO are loaded twice, one row per lane for those two
+// S = Q K^T and dP = dO V^T; parts y = 0 of all items start first); the rows of Q and dO are loaded twice, one row per lane for those two
 // products and coalesced for dV^T += dO^T P and dK^T += Q^T dS.
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_kv_f32_kernel(BwdArgs a) {

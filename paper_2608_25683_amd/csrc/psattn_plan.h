@@ -1,9 +1,11 @@
 // Work-plan records shared by the host planner and the HIP kernels.
 //
 // A plan turns a prefix forest into three lists of independent work items:
-//   * forward / dQ items: a tile of query rows of one node (or a piece of
-//     its key range) x the node's root-to-node key path x a chunk of query
-//     heads that read one kv head;
+//   * forward / dQ items: a tile of query rows of one node (or of packed
+//     siblings) x the node's root-to-node key path (or a piece of it) x a
+//     chunk of query heads that read one kv head; as launched in bf16, 8 of
+//     the (32-row subtile, query head) pairs of a tile and kv head, whatever
+//     the number of heads per kv head;
 //   * dK/dV items: a tile of keys of one node x one kv head x a chunk of the
 //     rows that consume those keys: every row of every descendant node (all
 //     branches reusing the prefix), then the node's own rows from its last
