@@ -254,6 +254,14 @@ std::vector<int> longest_first(const std::vector<double>& cost) {
   return ord;
 }
 
+// first, first + step, ..: n entries behind v's
+void append_run(std::vector<int32_t>& v, int64_t first, int64_t n, int step) {
+  const size_t at = v.size();
+  v.resize(at + (size_t)n);
+  int32_t* p = v.data() + at;
+  for (int64_t i = 0; i < n; ++i) p[i] = (int32_t)(first + step * i);
+}
+
 // Time of one pass over work items of the given costs on `cus` compute units, in the order of
 // longest_first (each free unit takes the next item).
 double makespan(std::vector<double>& cost, double cus) {
@@ -392,13 +400,12 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   t->row_pos.assign(t->Ns, 0);
   t->row_slot.assign(t->Ns, 0);
   for (int n = 0; n < N; ++n) {
-    for (int b = t->blk_ptr[n]; b < t->blk_ptr[n + 1]; ++b)
-      for (int k = 0; k < t->blocks[b].len; ++k) node_slots[n].push_back((int32_t)(t->blocks[b].base + k));
-    if (!t->ext[n])
-      for (int a = 0; a < t->seg_len[n]; ++a) {
-        t->row_pos[t->row_off[n] + a] = (int32_t)(t->off[n] + a);
-        t->row_slot[t->row_off[n] + a] = node_slots[n][a];
-      }
+    node_slots[n].reserve((size_t)t->seg_len[n]);
+    for (int b = t->blk_ptr[n]; b < t->blk_ptr[n + 1]; ++b) append_run(node_slots[n], t->blocks[b].base, t->blocks[b].len, 1);
+    if (!t->ext[n]) {
+      std::iota(t->row_pos.begin() + t->row_off[n], t->row_pos.begin() + t->row_off[n] + t->seg_len[n], (int32_t)t->off[n]);
+      std::copy(node_slots[n].begin(), node_slots[n].end(), t->row_slot.begin() + t->row_off[n]);
+    }
   }
 
   std::vector<int64_t> desc_rows(N, 0);   // rows of the (internal) descendants of each node
@@ -612,8 +619,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     rows_used += (int64_t)(npref + 1) * s.bmq;
     const int32_t q_pack = (int32_t)t->q_list.size();
     int rows = 0;
-    for (int n : pk)
-      for (int a = 0; a < t->seg_len[n]; ++a) t->q_list.push_back((int32_t)(t->row_off[n] + a));
+    for (int n : pk) append_run(t->q_list, t->row_off[n], t->seg_len[n], 1);
     for (int j = 0; j < npref; ++j) {
       const int64_t k0 = npref > 1 ? j * split_keys : 0;
       const int64_t k1 = npref > 1 ? std::min(pre, (j + 1) * split_keys) : pre;
@@ -657,7 +663,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       int a1 = std::min<int>(t->seg_len[n], a0 + s.bmq);
       int nq = a1 - a0;
       int32_t q_off = (int32_t)t->q_list.size();
-      for (int a = a0; a < a1; ++a) t->q_list.push_back((int32_t)(t->row_off[n] + a));
+      append_run(t->q_list, t->row_off[n] + a0, nq, 1);
       int64_t nkv_total = t->off[n] + a1;
       int64_t min_qpos = t->off[n] + a0;
       const int npieces = num_pieces(nkv_total);
@@ -700,6 +706,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     std::vector<double> c(ftasks.size());
     for (size_t i = 0; i < ftasks.size(); ++i) c[i] = ftasks[i].cost;
     t->fwd.clear();
+    t->fwd.reserve(ftasks.size() * n_chunks);
+    items.reserve((ftasks.size() + sib_items.size()) * n_chunks);
     for (int i : longest_first(c)) {
       const FTask& f = ftasks[i];
       int64_t full_by_len = f.nkv / KV_TILE;
@@ -731,7 +739,8 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
       items.push_back(f);
       items.back().head0 = j % t->hkv * s.g + j / t->hkv * s.hc;
     }
-  std::vector<std::pair<int64_t, int>> launch;   // (key tiles, item)
+  std::vector<int32_t> key_tiles_of(items.size(), -1);   // (-1: not launched)
+  int32_t most_tiles = 0;
   for (size_t i = 0; i < items.size(); ++i) {
     FwdItem& f = items[i];
     int64_t keys = f.nkv;
@@ -748,11 +757,17 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
         f.nkv = (int32_t)keys;
       }
     }
-    launch.push_back({(keys + KV_TILE - 1) / KV_TILE, (int)i});
+    key_tiles_of[i] = (int32_t)((keys + KV_TILE - 1) / KV_TILE);
+    most_tiles = std::max(most_tiles, key_tiles_of[i]);
   }
-  std::stable_sort(launch.begin(), launch.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-  t->fwd_launch.clear();
-  for (const auto& l : launch) t->fwd_launch.push_back(items[l.second]);
+  // (counting sort, most tiles first, equal ones in order)
+  std::vector<size_t> at((size_t)most_tiles + 2, 0);
+  for (int32_t n : key_tiles_of)
+    if (n >= 0) ++at[(size_t)(most_tiles - n) + 1];
+  for (size_t n = 1; n < at.size(); ++n) at[n] += at[n - 1];
+  t->fwd_launch.resize(at.back());
+  for (size_t i = 0; i < items.size(); ++i)
+    if (key_tiles_of[i] >= 0) t->fwd_launch[at[(size_t)(most_tiles - key_tiles_of[i])]++] = items[i];
 
   // ---------------- dK/dV tasks: key tile x consumer-row chunk ----------------
   // consumer list of node m: every row of every (internal) descendant (node order), then m's own
@@ -771,9 +786,9 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     }
     std::sort(sub.begin(), sub.end());
     for (int x : sub)
-      for (int a = 0; !t->ext[x] && a < t->seg_len[x]; ++a) t->q_list.push_back((int32_t)(t->row_off[x] + a));
+      if (!t->ext[x]) append_run(t->q_list, t->row_off[x], t->seg_len[x], 1);
     desc_len[m] = (int64_t)t->q_list.size() - cons_off[m];
-    for (int a = t->seg_len[m] - 1; !t->ext[m] && a >= 0; --a) t->q_list.push_back((int32_t)(t->row_off[m] + a));
+    if (!t->ext[m]) append_run(t->q_list, t->row_off[m] + t->seg_len[m] - 1, t->seg_len[m], -1);
     cons_len[m] = (int64_t)t->q_list.size() - cons_off[m];
     if (t->q_list.size() > (size_t)INT32_MAX) return fail(PSATTN_E_UNSUPPORTED, "row lists exceed 2^31 entries");
   }
@@ -917,6 +932,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
     });
     auto emit = [&](std::vector<BkvItem>& out) {
       out.clear();
+      out.reserve(ord.size() * (size_t)t->hkv);
       for (int i : ord) {
         const BTask& b = btasks[i];
         for (int hk = 0; hk < t->hkv; ++hk) {
@@ -971,9 +987,11 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   t->o_reduce = place(t->reduce.size() * sizeof(ReduceEntry));
   t->o_pad = place(t->pad_slots.size() * 4);
   t->plan_bytes = cur;
-  t->image.assign(cur, 0);
-  auto put = [&](size_t at, const void* p, size_t bytes) {
-    if (bytes) memcpy(t->image.data() + at, p, bytes);
+  t->image.clear();
+  t->image.reserve(cur);
+  auto put = [&](size_t at, const void* p, size_t bytes) {   // (in ascending order of at; zeros between)
+    if (t->image.size() < at) t->image.resize(at);
+    t->image.insert(t->image.end(), (const uint8_t*)p, (const uint8_t*)p + bytes);
   };
   put(t->o_row_pos, t->row_pos.data(), t->row_pos.size() * 4);
   put(t->o_row_slot, t->row_slot.data(), t->row_slot.size() * 4);
@@ -986,6 +1004,7 @@ psattn_status build_plan(psattn_tree* t, const psattn_plan_opts& o) {
   put(t->o_bkv, t->bkv_launch.data(), t->bkv_launch.size() * sizeof(BkvItem));
   put(t->o_reduce, t->reduce.data(), t->reduce.size() * sizeof(ReduceEntry));
   put(t->o_pad, t->pad_slots.data(), t->pad_slots.size() * 4);
+  t->image.resize(cur);
   return PSATTN_OK;
 }
 
