@@ -10,8 +10,8 @@ P = pytest.importorskip("paper_2608_25683_amd.psattn")
 from test_abi_host import _check_plan, _visible_pairs  # noqa: E402
 
 SHAPES = {   # name -> (parent, seg, samples, hq, hkv): what the automatic rules split
-    "long_range": ([-1, 0], [700, 20], [1], 8, 2),            # key ranges of few row tiles
-    "longer_range": ([-1, 0, 0], [1600, 40, 33], [1, 2], 5, 1),
+    "long_range": ([-1, 0], [700, 20], [1], 2, 1),            # key ranges of few row tiles
+    "long_range_odd": ([-1, 0, 0], [640, 40, 33], [1, 2], 3, 1),
     "few_branches": ([-1, 0, 0, 0], [260, 70, 33, 5], [1, 2, 3], 4, 2),
     "one_head": ([-1, 0, 0], [400, 130, 129], [1, 2], 5, 1),
     "short_siblings": ([-1] + [0] * 6, [330, 16, 9, 30, 1, 16, 64], list(range(1, 7)), 8, 2),
