@@ -968,7 +968,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 #pragma unroll
       for (int mb = 0; mb < DB; ++mb) pin_a(dq[rh][mb]);
   }
-  // rows that this pass leaves to the row-by-row one (packed siblings with results that are not finite)
+  // rows for the row-by-row pass below (packed siblings with results that are not finite)
   uint32_t redo[NH];
 #pragma unroll
   for (int rh = 0; rh < NH; ++rh) {
@@ -986,8 +986,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   // the fixed-order reduction of the pieces
 #pragma unroll
   for (int rh = 0; rh < NH; ++rh) {
-    const float e = pair_sum(eps[rh]);   // lanes l and l ^ 32 hold different keys of one row
-    if (hh == 0 && row_ok[rh] && !(redo[rh] >> l32 & 1)) {
+    const float e = eps[rh] = pair_sum(eps[rh]);   // lanes l and l ^ 32 hold different keys of one row
+    if (hh == 0 && row_ok[rh]) {
       if (it.part < 0) {
         const uint32_t w = split_bf16(-del[rh]);
         const float d0 = bf2f(w & 0xffffu) + bf2f(w >> 16);   // the -Delta the dP products started from
@@ -1008,7 +1008,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   const float scale = a.s.scale;
   auto redo_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int rh = 0; rh < NH; ++rh)
+    for (int rh = 0; rh < NH; ++rh) {
+      if (redo[rh]) __threadfence_block();   // (this wavefront's rows, written before, are read back)
 #pragma unroll 1
       for (uint32_t todo = redo[rh]; todo; todo &= todo - 1) {
         const int l = __builtin_ctz(todo);
@@ -1016,18 +1017,26 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
         const size_t pair = (size_t)__builtin_amdgcn_readlane(row[rh], l) * a.s.hq + head[rh];
         const uint32_t w = split_bf16(-lane_value(del[rh], l));
         const float d0 = bf2f(w & 0xffffu) + bf2f(w >> 16);   // as above
-        float x[D / 64];
-        const float e = row_dq<D, true>(x, path, (const bf16_t*)a.Q + pair * D, (const bf16_t*)a.dO + pair * D, Kb, Vb,
-                                        (size_t)a.s.hkv * D, a.s.scale, lane_value(lse2[rh], l) / kLog2e, d0, lane);
-        if (lane == 0) ((uint32_t*)a.kv_nd)[pair] = split_bf16(d0 - e);
+        const bool want_sum = !is_finite(lane_value(eps[rh], l));
+        float* const qp = a.dQ + pair * D + (D / 64) * lane;
+        float x[D / 64], sum;
+        bool want[D / 64];
 #pragma unroll
-        for (int i = 0; i < D / 64; ++i) a.dQ[pair * D + (D / 64) * lane + i] = x[i] * a.s.scale;
+        for (int e = 0; e < D / 64; ++e) want[e] = !is_finite(qp[e]);
+        if (!row_dq<D, true>(x, sum, want, want_sum, path, (const bf16_t*)a.Q + pair * D, (const bf16_t*)a.dO + pair * D, Kb, Vb,
+                             (size_t)a.s.hkv * D, a.s.scale, lane_value(lse2[rh], l) / kLog2e, d0, lane))
+          continue;
+        if (lane == 0 && want_sum) ((uint32_t*)a.kv_nd)[pair] = split_bf16(d0 - sum);
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e)
+          if (want[e]) qp[e] = x[e] * a.s.scale;
       }
+    }
   };
   if constexpr (NW * 32 * QS > NS * 2 * TB) {
 #pragma unroll
     for (int rh = 0; rh < NH; ++rh) {
-      if (!row_ok[rh] || (redo[rh] >> l32 & 1)) continue;
+      if (!row_ok[rh]) continue;
       float* dst = it.part < 0 ? a.dQ + ((size_t)row[rh] * a.s.hq + head[rh]) * D
                                : a.part_dq + (((size_t)it.part + ridx[rh]) * a.s.hq + head[rh]) * D;
 #pragma unroll
@@ -1062,7 +1071,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
       const int rl = k * RPIQ + lane / CPRQ;
       const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)dsto, rl);
       const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(dsto >> 32), rl);
-      const int ok = __shfl((int)(row_ok[rh] && !(redo[rh] >> l32 & 1)), rl);
+      const int ok = __shfl((int)row_ok[rh], rl);
       const u32x4 v = *(const u32x4*)(qt + rl * QS + 16 * ch);
       if (ok) *(u32x4*)(base + (((size_t)hi << 32) | lo) + 4 * ch) = v;
     }

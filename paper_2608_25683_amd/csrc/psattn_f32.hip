@@ -207,21 +207,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, D == 128
     z = add_if_finite(x[c], z);
   }
   const uint64_t redo = redo_lanes<SIB>(it, row_ok && !(z == 0.f));
-  if (row_ok && !(redo >> lane & 1)) {
+  if (row_ok) {
 #pragma unroll
     for (int c = 0; c < D / 32; ++c) *(f32x4*)(op + 4 * ((tid & 7) + 8 * c)) = x[c];
   }
   if constexpr (SIB) {
+    if (redo) __threadfence_block();   // (this wavefront's rows, written above, are read back)
     for (uint64_t todo = redo & 0x0101010101010101ull; todo; todo &= todo - 1) {   // the row's first thread
       const int l = __builtin_ctzll(todo), i = 8 * wave + l / 8;
+      if (!(lane_value(inv, l) > 0.f)) continue;   // no sum of probabilities: not finite by its own scores
       const int qpos = a.plan.q_pos[it.q_off + i];
       const RowKeys keys = row_keys<SIB>(it, it.nkv, i, qpos);
       const size_t at = ((size_t)__builtin_amdgcn_readlane(orow, l) * a.s.hq + head) * D;
+      float* const yp = (float*)a.O + at + (D / 64) * lane;
       float y[D / 64];
-      row_fwd<D, false>(y, RowPath(kvl, it, keys.lim, (int)keys.gap), (const float*)a.Q + at, Kh, Vh, kv_stride,
-                        a.s.scale, lane_value(m, l), lane_value(inv, l), lane);
+      bool want[D / 64];
 #pragma unroll
-      for (int e = 0; e < D / 64; ++e) ((float*)a.O)[at + (D / 64) * lane + e] = y[e];
+      for (int e = 0; e < D / 64; ++e) want[e] = !is_finite(yp[e]);
+      if (!row_fwd<D, false>(y, want, RowPath(kvl, it, keys.lim, (int)keys.gap), (const float*)a.Q + at, Kh, Vh, kv_stride,
+                             a.s.scale, lane_value(m, l), lane_value(inv, l), lane))
+        continue;
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e)
+        if (want[e]) yp[e] = y[e];
     }
   }
 }
@@ -297,22 +305,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     z = add_if_finite(x[c], z);
   }
   const uint64_t redo = redo_lanes<SIB>(it, row_ok && !(z == 0.f));
-  if (row_ok && !(redo >> lane & 1)) {
+  if (row_ok) {
 #pragma unroll
     for (int c = 0; c < D / 32; ++c) *(f32x4*)(dst + 4 * ((tid & 7) + 8 * c)) = x[c];
   }
   if constexpr (SIB) {
+    if (redo) __threadfence_block();   // (this wavefront's rows, written above, are read back)
     for (uint64_t todo = redo & 0x0101010101010101ull; todo; todo &= todo - 1) {   // the row's first thread
       const int i = 8 * wave + __builtin_ctzll(todo) / 8;
       const int qrow = a.plan.q_list[it.q_off + i], qpos = a.plan.q_pos[it.q_off + i];
       const RowKeys keys = row_keys<SIB>(it, it.nkv, i, qpos);
       const size_t at = ((size_t)qrow * a.s.hq + head) * D;
-      float y[D / 64];
-      row_dq<D, false>(y, RowPath(kvl, it, keys.lim, (int)keys.gap), (const float*)a.Q + at, (const float*)a.dO + at, Kh, Vh,
-                       kv_stride, a.s.scale, a.LSE[(size_t)head * a.s.ns + qrow],
-                       -a.delta[(size_t)qrow * a.s.hq + head], lane);
+      float* const yp = a.dQ + at + (D / 64) * lane;
+      float y[D / 64], sum;
+      bool want[D / 64];
 #pragma unroll
-      for (int e = 0; e < D / 64; ++e) a.dQ[at + (D / 64) * lane + e] = y[e] * a.s.scale;
+      for (int e = 0; e < D / 64; ++e) want[e] = !is_finite(yp[e]);
+      if (!row_dq<D, false>(y, sum, want, false, RowPath(kvl, it, keys.lim, (int)keys.gap), (const float*)a.Q + at,
+                            (const float*)a.dO + at, Kh, Vh, kv_stride, a.s.scale, a.LSE[(size_t)head * a.s.ns + qrow],
+                            -a.delta[(size_t)qrow * a.s.hq + head], lane))
+        continue;
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e)
+        if (want[e]) yp[e] = y[e] * a.s.scale;
     }
   }
 }

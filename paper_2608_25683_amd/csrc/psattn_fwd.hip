@@ -417,7 +417,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
 #pragma unroll
       for (int mb = 0; mb < DB; ++mb) pin_a(oacc[rh][mb]);
   }
-  // rows that this pass leaves to the row-by-row one (packed siblings with results that are not finite)
+  // rows for the row-by-row pass below (packed siblings with results that are not finite)
   uint32_t redo[NH];
 #pragma unroll
   for (int rh = 0; rh < NH; ++rh) {
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
         const int rl = k * RPIO + lane / CPRO;          // staged row; its half is (k * RPIO) / 32
         const int rh = (k * RPIO) / 32;
         const int r = __shfl(row[rh], rl % 32);
-        const int ok = __shfl((int)(row_ok[rh] && !(redo[rh] >> l32 & 1)), rl % 32);
+        const int ok = __shfl((int)row_ok[rh], rl % 32);
         const u32x4 v = *(const u32x4*)(ot + rl * OS + 16 * ch);
         if (ok) *(u32x4*)(dst + ((size_t)r * a.s.hq + head[rh]) * RB + 16 * ch) = v;
       }
@@ -505,23 +505,32 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3 - NH,
   }
   if constexpr (SIB) {
 #pragma unroll
-    for (int rh = 0; rh < NH; ++rh)
+    for (int rh = 0; rh < NH; ++rh) {
+      if (redo[rh]) __threadfence_block();   // (this wavefront's rows, written above, are read back)
 #pragma unroll 1
       for (uint32_t todo = redo[rh]; todo; todo &= todo - 1) {
         const int l = __builtin_ctz(todo);
+        const float row_inv = lane_value(inv[rh], l);
+        if (!(row_inv > 0.f)) continue;   // no sum of probabilities: not finite by its own scores
         const RowPath path(kvl, it, __builtin_amdgcn_readlane(lim[rh], l), __builtin_amdgcn_readlane((int)gap[rh], l));
         const size_t at = ((size_t)__builtin_amdgcn_readlane(row[rh], l) * a.s.hq + head[rh]) * D;
+        bf16_t* const op = (bf16_t*)a.O + at + (D / 64) * lane;
         float o[D / 64];
-        row_fwd<D, true>(o, path, (const bf16_t*)a.Q + at, Kb, Vb, (size_t)a.s.hkv * D, a.s.scale,
-                         lane_value(m_run[rh], l) * a.s.scale, lane_value(inv[rh], l), lane);
+        bool want[D / 64];
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) want[e] = !is_finite(bf2f(op[e]));
+        if (!row_fwd<D, true>(o, want, path, (const bf16_t*)a.Q + at, Kb, Vb, (size_t)a.s.hkv * D, a.s.scale,
+                              lane_value(m_run[rh], l) * a.s.scale, row_inv, lane))
+          continue;
 #pragma unroll
         for (int e = 0; e < D / 64; ++e) {
+          if (!want[e]) continue;
           const uint32_t w = split_bf16(o[e]);
-          const size_t i = at + (D / 64) * lane + e;
-          ((bf16_t*)a.O)[i] = (bf16_t)w;
-          if (a.O_lo) ((bf16_t*)a.O_lo)[i] = (bf16_t)(w >> 16);
+          op[e] = (bf16_t)w;
+          if (a.O_lo) ((bf16_t*)a.O_lo)[at + (D / 64) * lane + e] = (bf16_t)(w >> 16);
         }
       }
+    }
   }
 }
 

@@ -64,3 +64,35 @@ def test_siblings_do_not_see_each_other(dtype, hq, hkv, d, kind):
     # the spoilt sibling itself: its last row sees the value (huge_v: a finite one)
     last = num(O)[rows[bad][-1]]
     assert np.isfinite(last).all() == (kind == "huge_v")
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d", [("bf16", 8, 2, 128), ("bf16", 5, 1, 64), ("fp32", 4, 2, 128), ("fp32", 3, 1, 64)])
+def test_only_the_rows_own_values_are_not_finite(dtype, hq, hkv, d):
+    """A NaN in the common prefix reaches every row, in its own column; beside it, an infinity in another column of
+    one sibling reaches that sibling's last row alone.  Columns without either keep their bits."""
+    from paper_2608_25683_amd import psattn as P
+    seg = SEG[dtype]
+    wl = W.custom([-1] + [0] * (len(seg) - 1), seg, list(range(1, len(seg))), hq=hq, hkv=hkv, d=d, dtype=dtype, seed=82,
+                  block_policy=lambda n: W.blocks_fixed(n, 16))
+    t = wl.tree
+    tree = P.Tree.from_workload(wl, device="cuda")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to("cuda").to(dt)
+    Q, K, V = up(wl.Q), up(wl.K_pool), up(wl.V_pool)
+    slots = t.row_slots()
+    rows = [np.arange(int(o), int(o) + int(n)) for o, n in zip(t.row_off, t.seg_len)]
+    clean, lse = P.psattn_fwd(tree, Q, K, V)
+    bad = 3
+    V[int(slots[rows[0][-1]]), :, 3] = float("nan")
+    V[int(slots[rows[bad][-1]]), :, 7] = float("inf")
+    print(f"siblings' columns {dtype} {hq}/{hkv} d={d}", file=sys.stderr, flush=True)
+    for lo in (None, torch.empty_like(Q)) if dtype == "bf16" else (None,):
+        O, LSE = P.psattn_fwd(tree, Q, K, V, O_lo=lo)
+        torch.cuda.synchronize()
+        keep = torch.from_numpy(np.concatenate([r for n, r in enumerate(rows) if n not in (0, bad)])).cuda()
+        cols = torch.tensor([c for c in range(d) if c not in (3, 7)], device="cuda")
+        assert torch.equal(LSE[:, keep], lse[:, keep])
+        assert torch.equal(O[keep][:, :, cols], clean[keep][:, :, cols])
+        assert torch.isnan(O[keep][:, :, 3]).all()
+        H.compare("column 7", O[keep][:, :, 7].double().cpu().numpy(), H.run_oracle(wl)[0][keep.cpu().numpy()][:, :, 7], dtype)
+        assert torch.isinf(O[int(rows[bad][-1]), :, 7]).all()
